@@ -214,111 +214,157 @@ __device__ inline bool is_ancestor_or_self(const Cell& A, const Cell& B) {
     return (B.ix >> s) == A.ix && (B.iy >> s) == A.iy && (B.iz >> s) == A.iz;
 }
 
-// U, W, X of cell b: counted (items == nullptr) or written at the offsets.
-// Ancestor chains are walked only when some ancestor has a leaf colleague
-// (cflag bit 1).
-__device__ inline void uwx_cell(const Cell* __restrict__ cells, int b,
-                                const int32_t* __restrict__ coll,
-                                const uint8_t* __restrict__ cflag, bool fill,
-                                const int32_t* __restrict__ ou, const int32_t* __restrict__ ow,
-                                const int32_t* __restrict__ ox, int32_t* __restrict__ iu,
-                                int32_t* __restrict__ iw, int32_t* __restrict__ ix, int& nu,
-                                int& nw, int& nx) {
-    Cell B = cells[b];
-    const bool walk = (cflag[b] & 2) != 0;
-    int32_t* pu = fill ? iu + ou[b] : nullptr;
-    int32_t* pw = fill ? iw + ow[b] : nullptr;
-    int32_t* px = fill ? ix + ox[b] : nullptr;
-    const bool leaf = B.nchild == 0;
-    // X(B): leaves C coarser than B in colleagues of ancestors, adjacent to
-    // parent(B) and not to B
-    if (B.level >= 2 && walk) {
-        Cell P = cells[B.parent];
-        for (int A = B.parent; A >= 0; A = cells[A].parent) {
-            const int32_t* ca = coll + (int64_t)A * kColl;
-            for (int q = 0; q < kColl; ++q) {
-                int C = ca[q];
-                if (C < 0) continue;
-                Cell cc = cells[C];
-                if (cc.nchild != 0) continue;
-                if (cells_adjacent(cc, P) && !cells_adjacent(cc, B)) {
-                    if (fill) px[nx] = C;
-                    ++nx;
-                }
-            }
-        }
+// The list traversals take 32 lanes (half a wave) per cell or target box.
+// They are bound by the latency of their dependent loads (ancestor ->
+// colleagues -> cells; node -> children): one thread per cell made each of
+// the 27 colleague reads of every ancestor, and each child of every node, a
+// dependent step of its own (210 us a pass for the 700 cells of 1000 Plummer
+// particles, 385 us at N = 2^22); with the lanes over the colleagues and over
+// (4 nodes) x (8 children) a cell takes 3 dependent loads per ancestor and 1
+// per level of descent (a whole evaluation of 1000 Plummer particles: 1098 ->
+// 679 us).  Half a wave is the least that holds the 27
+// colleagues; a whole wave per cell would leave 37 lanes idle there.
+//
+// One output list of a half wave: the lanes with `on` append their item in
+// lane order (p == nullptr: only counted).  Every lane of the half calls.
+struct HalfList {
+    int32_t* p;
+    int n;
+    __device__ __forceinline__ void put(bool on, int item) {
+        const int lane = threadIdx.x & 63;
+        const uint32_t m = (uint32_t)(__ballot(on) >> (lane & 32));
+        if (p && on) p[n + __popc(m & ((1u << (lane & 31)) - 1u))] = item;
+        n += __popc(m);
     }
-    if (leaf) {
-        // coarser adjacent leaves: leaf colleagues of proper ancestors
-        for (int A = walk ? B.parent : -1; A >= 0; A = cells[A].parent) {
-            const int32_t* ca = coll + (int64_t)A * kColl;
-            for (int q = 0; q < kColl; ++q) {
-                int C = ca[q];
-                if (C < 0) continue;
-                Cell cc = cells[C];
-                if (cc.nchild == 0 && cells_adjacent(cc, B)) {
-                    if (fill) pu[nu] = C;
-                    ++nu;
-                }
-            }
+};
+
+// Stack of one half wave in LDS: opened nodes as (first child, children - 1)
+// in one word (a first child is below 2^29: the V table alone holds 864 bytes
+// per cell).  A step takes the 4 top nodes and pushes at most 32; nodes are
+// ordered by level, deepest on top, and a level is pushed to only when the
+// deeper ones were taken in the same step, so a level holds at most 32 (the
+// colleagues at the start: 27) and the 21 levels at most 27 + 20 * 32 = 667.
+constexpr int kHalfStack = 672;
+
+__device__ __forceinline__ uint32_t half_node(const Cell& c) {
+    return ((uint32_t)c.child << 3) | (uint32_t)(c.nchild - 1);
+}
+
+// pushes the nodes of the lanes with `on`; false when they do not fit
+__device__ __forceinline__ bool half_push(uint32_t* st, int& sp, bool on, uint32_t node) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t m = (uint32_t)(__ballot(on) >> (lane & 32));
+    const int at = sp + __popc(m & ((1u << (lane & 31)) - 1u));
+    if (sp + __popc(m) > kHalfStack) return false;
+    wave_lds_fence();
+    if (on) st[at] = node;
+    sp += __popc(m);
+    wave_lds_fence();
+    return true;
+}
+
+// Below the stacked nodes: leaves adjacent to B (near) and the first cells
+// not adjacent to B (far); adjacent inner cells are opened.  False when the
+// stack overflowed.
+__device__ inline bool half_descend(const Cell* __restrict__ cells, const Cell& B, uint32_t* st,
+                                    int sp, HalfList& near, HalfList& far) {
+    const int hl = threadIdx.x & 31;
+    bool ok = true;
+    while (sp > 0) {
+        const int k = min(sp, 4);
+        sp -= k;
+        const uint32_t nd = st[sp + min(hl >> 3, k - 1)];
+        const bool have = (hl >> 3) < k && (hl & 7) <= (int)(nd & 7u);
+        const int D = (int)(nd >> 3) + (hl & 7);
+        Cell d;
+        d.nchild = 0;
+        if (have) d = cells[D];
+        const bool adj = have && cells_adjacent(d, B);
+        near.put(adj && d.nchild == 0, D);
+        far.put(have && !adj, D);
+        const bool open = adj && d.nchild != 0;
+        ok &= half_push(st, sp, open, open ? half_node(d) : 0u);
+    }
+    return ok;
+}
+
+// Leaf colleagues of cell A and of the cells above it, from A up: adj(C, cc)
+// is called once per ancestor that has one, with C < 0 in the lanes without.
+// cflag ends the walk at the last such ancestor.
+template <typename F>
+__device__ __forceinline__ void half_walk(const Cell* __restrict__ cells, int A,
+                                          const int32_t* __restrict__ coll,
+                                          const uint8_t* __restrict__ cflag, F&& each) {
+    const int hl = threadIdx.x & 31;
+    while (A >= 0) {
+        const int f = cflag[A], up = cells[A].parent;
+        if (f & 1) {
+            int C = hl < kColl ? coll[(int64_t)A * kColl + hl] : -1;
+            Cell cc;
+            cc.nchild = 1;
+            if (C >= 0) cc = cells[C];
+            if (cc.nchild != 0) C = -1;
+            each(C, cc);
         }
-        // same level, then finer adjacent leaves (U) and W by descent
-        const int32_t* cb = coll + (int64_t)b * kColl;
-        int stack[kStack];
-        for (int q = 0; q < kColl; ++q) {
-            int C = cb[q];
-            if (C < 0) continue;
-            Cell cc = cells[C];
-            if (cc.nchild == 0) {
-                if (fill) pu[nu] = C;
-                ++nu;
-                continue;
-            }
-            if (C == b) continue;
-            int sp = 0;
-            stack[sp++] = C;
-            while (sp > 0) {
-                Cell cur = cells[stack[--sp]];
-                for (int i = cur.nchild - 1; i >= 0; --i) {
-                    int D = cur.child + i;
-                    Cell d = cells[D];
-                    if (cells_adjacent(d, B)) {
-                        if (d.nchild == 0) {
-                            if (fill) pu[nu] = D;
-                            ++nu;
-                        } else if (sp < kStack) {
-                            stack[sp++] = D;
-                        }
-                    } else {
-                        if (fill) pw[nw] = D;
-                        ++nw;
-                    }
-                }
-            }
-        }
+        if (!(f & 2)) break;
+        A = up;
     }
 }
 
 // Count pass (iu == nullptr): cu, cw, cx per cell (entry nc of these and
 // of cv set to 0); fill pass: the items.
-__global__ void k_uwx(const Cell* __restrict__ cells, int nc, const int32_t* __restrict__ coll,
-                      const uint8_t* __restrict__ cflag, int32_t* __restrict__ cu,
-                      int32_t* __restrict__ cw, int32_t* __restrict__ cx,
-                      int32_t* __restrict__ cv, int32_t* __restrict__ cf,
-                      const int32_t* __restrict__ ou,
-                      const int32_t* __restrict__ ow, const int32_t* __restrict__ ox,
-                      int32_t* __restrict__ iu, int32_t* __restrict__ iw,
-                      int32_t* __restrict__ ix) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256)
+k_uwx(const Cell* __restrict__ cells, int nc, const int32_t* __restrict__ coll,
+      const uint8_t* __restrict__ cflag, int32_t* __restrict__ cu, int32_t* __restrict__ cw,
+      int32_t* __restrict__ cx, int32_t* __restrict__ cv, int32_t* __restrict__ cf,
+      const int32_t* __restrict__ ou, const int32_t* __restrict__ ow,
+      const int32_t* __restrict__ ox, int32_t* __restrict__ iu, int32_t* __restrict__ iw,
+      int32_t* __restrict__ ix) {
+    __shared__ uint32_t stk[8][kHalfStack];
+    const int hl = threadIdx.x & 31;
+    const int b = blockIdx.x * 8 + (int)(threadIdx.x >> 5);
     const bool fill = iu != nullptr;
-    int nu = 0, nw = 0, nx = 0;
-    if (b < nc) uwx_cell(cells, b, coll, cflag, fill, ou, ow, ox, iu, iw, ix, nu, nw, nx);
+    HalfList U{nullptr, 0}, Wl{nullptr, 0}, X{nullptr, 0};
+    if (b < nc) {
+        const Cell B = cells[b];
+        const bool walk = (cflag[b] & 2) != 0, leaf = B.nchild == 0;
+        if (fill) {
+            X.p = ix + ox[b];
+            if (leaf) {
+                U.p = iu + ou[b];
+                Wl.p = iw + ow[b];
+            }
+        }
+        // leaf colleagues of the proper ancestors: coarser adjacent leaves (U
+        // of a leaf), and those adjacent to the parent only (X)
+        if (walk && (leaf || B.level >= 2)) {
+            const Cell P = cells[B.parent];
+            half_walk(cells, B.parent, coll, cflag, [&](int C, const Cell& cc) {
+                const bool near = C >= 0 && cells_adjacent(cc, B);
+                if (leaf) U.put(near, C);
+                if (B.level >= 2) X.put(C >= 0 && !near && cells_adjacent(cc, P), C);
+            });
+        }
+        // same level, then finer adjacent leaves (U) and W by descent
+        if (leaf) {
+            const int C = hl < kColl ? coll[(int64_t)b * kColl + hl] : -1;
+            Cell cc;
+            cc.nchild = 0;
+            if (C >= 0) cc = cells[C];
+            U.put(C >= 0 && cc.nchild == 0, C);
+            uint32_t* st = stk[threadIdx.x >> 5];
+            int sp = 0;
+            const bool open = cc.nchild != 0;
+            half_push(st, sp, open, open ? half_node(cc) : 0u);
+            half_descend(cells, B, st, sp, U, Wl);
+        }
+    }
     if (fill) return;
-    if (b <= nc) {  // entry nc is 0: the five arrays are scanned as one
-        cu[b] = nu;
-        cw[b] = nw;
-        cx[b] = nx;
-        cf[b] = nx > 0 ? 1 : 0;  // cells with an X list (P2L targets)
+    if (b <= nc && hl == 0) {  // entry nc is 0: the five arrays are scanned as one
+        cu[b] = U.n;
+        cw[b] = Wl.n;
+        cx[b] = X.n;
+        cf[b] = X.n > 0 ? 1 : 0;  // cells with an X list (P2L targets)
         if (b == nc) cv[b] = 0;
     }
 }
@@ -349,147 +395,98 @@ __global__ void k_x_cells(const int32_t* __restrict__ foff, int nc, int32_t* __r
 // box's own leaf (or host) and of every cell above it, and with
 // BOX_TREECODE_FULL far takes their V lists too (at p = 3 the far kernel
 // reads those from the V table itself).
-__device__ void box_lists_one(const Cell* __restrict__ cells, int ncells,
-                              const int32_t* __restrict__ coll,
-                              const int32_t* __restrict__ vsrc,
-                              const int32_t* __restrict__ x_off,
-                              const int32_t* __restrict__ x_items, const TBox& bx, int mode,
-                              int32_t* pn, int32_t* pf, int& nn, int& nf, bool& over) {
+__device__ inline bool box_lists_one(const Cell* __restrict__ cells, int ncells,
+                                     const int32_t* __restrict__ coll,
+                                     const uint8_t* __restrict__ cflag,
+                                     const int32_t* __restrict__ vsrc,
+                                     const int32_t* __restrict__ x_off,
+                                     const int32_t* __restrict__ x_items, const TBox& bx,
+                                     int mode, uint32_t* st, HalfList& near, HalfList& far) {
+    const int hl = threadIdx.x & 31;
     const Cell B = box_cell(bx);
     const bool src = bx.leaf >= 0;
     const int P = src ? cells[bx.leaf].parent : bx.host;
-    // coarser adjacent leaves: leaf colleagues of the cells above the box
-    for (int A = P; A >= 0; A = cells[A].parent) {
-        const int32_t* ca = coll + (int64_t)A * kColl;
-        for (int q = 0; q < kColl; ++q) {
-            const int C = ca[q];
-            if (C < 0) continue;
-            const Cell cc = cells[C];
-            if (cc.nchild == 0 && cells_adjacent(cc, B)) {
-                if (pn) pn[nn] = C;
-                ++nn;
-            }
-        }
-    }
+    // leaf colleagues of the cells above the box: coarser adjacent leaves
+    // (U), and for a box without sources those adjacent to P only (X)
+    const bool has_x = !src && P >= 0 && B.level >= 2;
+    Cell Pc = B;
+    if (has_x) Pc = cells[P];
+    half_walk(cells, P, coll, cflag, [&](int C, const Cell& cc) {
+        const bool adj = C >= 0 && cells_adjacent(cc, B);
+        near.put(adj || (has_x && C >= 0 && cells_adjacent(cc, Pc)), C);
+    });
     // colleagues of the box: leaves (U), and below the others finer
     // adjacent leaves (U) and the first non-adjacent cells (W)
-    int stack[kStack];
-    for (int q = 0; q < kColl; ++q) {
-        const int ex = q / 9 - 1, ey = (q / 3) % 3 - 1, ez = q % 3 - 1;
-        int C;
+    int C = -1;
+    if (hl < kColl) {
+        const int ex = hl / 9 - 1, ey = (hl / 3) % 3 - 1, ez = hl % 3 - 1;
         if (P >= 0)
             C = cell_at_offset(cells, coll + (int64_t)P * kColl, B, ex, ey, ez);
         else  // level 0: the root is the only cell
             C = (ncells > 0 && B.ix + ex == 0 && B.iy + ey == 0 && B.iz + ez == 0) ? 0 : -1;
-        if (C < 0) continue;
-        const Cell cc = cells[C];
-        if (cc.nchild == 0) {
-            if (pn) pn[nn] = C;
-            ++nn;
-            continue;
-        }
-        int sp = 0;
-        stack[sp++] = C;
-        while (sp > 0) {
-            const Cell cur = cells[stack[--sp]];
-            for (int i = cur.nchild - 1; i >= 0; --i) {
-                const int D = cur.child + i;
-                const Cell d = cells[D];
-                if (cells_adjacent(d, B)) {
-                    if (d.nchild == 0) {
-                        if (pn) pn[nn] = D;
-                        ++nn;
-                    } else if (sp < kStack) {
-                        stack[sp++] = D;
-                    } else {
-                        over = true;
-                    }
-                } else {
-                    if (pf) pf[nf] = D;
-                    ++nf;
-                }
-            }
-        }
     }
+    Cell cc;
+    cc.nchild = 0;
+    if (C >= 0) cc = cells[C];
+    near.put(C >= 0 && cc.nchild == 0, C);
+    int sp = 0;
+    const bool open = cc.nchild != 0;
+    bool ok = half_push(st, sp, open, open ? half_node(cc) : 0u);
+    ok &= half_descend(cells, B, st, sp, near, far);
     if (!src) {
         // V: children of the colleagues of P not adjacent to the box
         // (outside the root: the root when it is not adjacent)
         if (P >= 0) {
             if (B.level >= 2) {
-                const int32_t* cp = coll + (int64_t)P * kColl;
-                for (int q = 0; q < kColl; ++q) {
-                    const int K = cp[q];
-                    if (K < 0) continue;
-                    const Cell kc = cells[K];
-                    for (int i = 0; i < kc.nchild; ++i) {
-                        const int D = kc.child + i;
-                        if (!cells_adjacent(cells[D], B)) {
-                            if (pf) pf[nf] = D;
-                            ++nf;
-                        }
-                    }
+                const int K = hl < kColl ? coll[(int64_t)P * kColl + hl] : -1;
+                Cell kc;
+                kc.nchild = 0;
+                kc.child = 0;
+                if (K >= 0) kc = cells[K];
+                for (int i = 0; i < 8; ++i) {
+                    const int D = kc.child + i;
+                    far.put(i < kc.nchild && !cells_adjacent(cells[i < kc.nchild ? D : 0], B), D);
                 }
             }
-        } else if (ncells > 0 && !cells_adjacent(cells[0], B)) {
-            if (pf) pf[nf] = 0;
-            ++nf;
-        }
-        // X: leaf colleagues of P and of the cells above it, adjacent to P
-        // and not to the box
-        if (P >= 0 && B.level >= 2) {
-            const Cell Pc = cells[P];
-            for (int A = P; A >= 0; A = cells[A].parent) {
-                const int32_t* ca = coll + (int64_t)A * kColl;
-                for (int q = 0; q < kColl; ++q) {
-                    const int C = ca[q];
-                    if (C < 0) continue;
-                    const Cell cc = cells[C];
-                    if (cc.nchild == 0 && cells_adjacent(cc, Pc) && !cells_adjacent(cc, B)) {
-                        if (pn) pn[nn] = C;
-                        ++nn;
-                    }
-                }
-            }
+        } else {
+            far.put(hl == 0 && ncells > 0 && !cells_adjacent(cells[0], B), 0);
         }
     }
     if (mode != BOX_FMM) {
         for (int A = src ? bx.leaf : P; A >= 0; A = cells[A].parent) {
-            for (int e = x_off[A]; e < x_off[A + 1]; ++e) {
-                if (pn) pn[nn] = x_items[e];
-                ++nn;
-            }
+            const int e0 = x_off[A], e1 = x_off[A + 1];
+            for (int e = e0; e < e1; e += 32)
+                near.put(e + hl < e1, e + hl < e1 ? x_items[e + hl] : 0);
             if (mode == BOX_TREECODE_FULL)
-                for (int q = 0; q < kSlots; ++q) {
-                    const int v = vsrc[(int64_t)A * kSlots + q];
-                    if (v >= 0) {
-                        if (pf) pf[nf] = v;
-                        ++nf;
-                    }
+                for (int q = 0; q < kSlots; q += 32) {
+                    const int v = q + hl < kSlots ? vsrc[(int64_t)A * kSlots + q + hl] : -1;
+                    far.put(v >= 0, v);
                 }
         }
     }
+    return ok;
 }
 
 // count pass (in == nullptr): cn, cf per box; fill pass: the items
-__global__ void k_box_lists(const Cell* __restrict__ cells, int ncells, Targets tg,
-                            const int32_t* __restrict__ coll, const int32_t* __restrict__ vsrc,
-                            const int32_t* __restrict__ x_off,
-                            const int32_t* __restrict__ x_items, int mode,
-                            int32_t* __restrict__ cn, int32_t* __restrict__ cf,
-                            const int32_t* __restrict__ on, const int32_t* __restrict__ of,
-                            int32_t* __restrict__ in, int32_t* __restrict__ inf,
-                            int32_t* __restrict__ status) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= tg.nbox) return;
+__global__ void __launch_bounds__(256)
+k_box_lists(const Cell* __restrict__ cells, int ncells, Targets tg,
+            const int32_t* __restrict__ coll, const uint8_t* __restrict__ cflag,
+            const int32_t* __restrict__ vsrc, const int32_t* __restrict__ x_off,
+            const int32_t* __restrict__ x_items, int mode, int32_t* __restrict__ cn,
+            int32_t* __restrict__ cf, const int32_t* __restrict__ on,
+            const int32_t* __restrict__ of, int32_t* __restrict__ in,
+            int32_t* __restrict__ inf, int32_t* __restrict__ status) {
+    __shared__ uint32_t stk[8][kHalfStack];
+    const int b = blockIdx.x * 8 + (int)(threadIdx.x >> 5);
+    if (b >= tg.nbox) return;  // uniform per half; no block-wide barrier below
     const TBox bx = tg.box[b];
-    int nn = 0, nf = 0;
-    bool over = false;
-    box_lists_one(cells, ncells, coll, vsrc, x_off, x_items, bx, mode, in ? in + on[b] : nullptr,
-                  inf ? inf + of[b] : nullptr, nn, nf, over);
-    if (!in) {
-        cn[b] = nn;
-        cf[b] = nf;
-        if (over) atomicOr(status, (int32_t)ST_OVERFLOW);
+    HalfList near{in ? in + on[b] : nullptr, 0}, far{inf ? inf + of[b] : nullptr, 0};
+    const bool ok = box_lists_one(cells, ncells, coll, cflag, vsrc, x_off, x_items, bx, mode,
+                                  stk[threadIdx.x >> 5], near, far);
+    if (!in && (threadIdx.x & 31) == 0) {
+        cn[b] = near.n;
+        cf[b] = far.n;
+        if (!ok) atomicOr(status, (int32_t)ST_OVERFLOW);
     }
 }
 
@@ -499,8 +496,8 @@ void build_box_lists(Tree& t, const Targets& tg, int mode, hipStream_t s) {
     const int nb = tg.nbox;
     int32_t* cnt = A.down<int32_t>(2 * (size_t)(nb + 1));
     int32_t *cn = cnt, *cf = cnt + nb + 1;
-    hipLaunchKernelGGL(k_box_lists, dim3(grid_for(nb, 64)), dim3(64), 0, s, t.cells, t.ncells,
-                       tg, t.coll, t.vsrc, t.x_off, t.x_items, mode, cn, cf, nullptr, nullptr,
+    hipLaunchKernelGGL(k_box_lists, dim3(grid_for(nb, 8)), dim3(256), 0, s, t.cells, t.ncells,
+                       tg, t.coll, t.cflag, t.vsrc, t.x_off, t.x_items, mode, cn, cf, nullptr, nullptr,
                        nullptr, nullptr, t.status);
     LAUNCH_CHECK();
     t.tn_off = A.up<int32_t>(nb + 1);
@@ -515,8 +512,8 @@ void build_box_lists(Tree& t, const Targets& tg, int mode, hipStream_t s) {
     t.tg_far = h[1];
     t.tn_items = A.up<int32_t>(std::max<int64_t>(t.tg_near, 1));
     t.tf_items = A.up<int32_t>(std::max<int64_t>(t.tg_far, 1));
-    hipLaunchKernelGGL(k_box_lists, dim3(grid_for(nb, 64)), dim3(64), 0, s, t.cells, t.ncells,
-                       tg, t.coll, t.vsrc, t.x_off, t.x_items, mode, nullptr, nullptr, t.tn_off,
+    hipLaunchKernelGGL(k_box_lists, dim3(grid_for(nb, 8)), dim3(256), 0, s, t.cells, t.ncells,
+                       tg, t.coll, t.cflag, t.vsrc, t.x_off, t.x_items, mode, nullptr, nullptr, t.tn_off,
                        t.tf_off, t.tn_items, t.tf_items, t.status);
     LAUNCH_CHECK();
 }
@@ -616,7 +613,7 @@ void build_fmm_lists(Tree& t, hipStream_t s) {
     hipLaunchKernelGGL(k_vlist, dim3(grid_for((int64_t)(nc + 1) / 2 * 64, 256)), dim3(256), 0,
                        s, t.cells, nc, t.coll, t.vsrc, cv, vcls, vmask);
     LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_uwx, dim3(grid_for(nc + 1, 64)), dim3(64), 0, s, t.cells, nc, t.coll,
+    hipLaunchKernelGGL(k_uwx, dim3(grid_for(nc + 1, 8)), dim3(256), 0, s, t.cells, nc, t.coll,
                        t.cflag, cu, cw, cx, cv, cf, nullptr, nullptr, nullptr, nullptr,
                        nullptr, nullptr);
     LAUNCH_CHECK();
@@ -655,7 +652,7 @@ void build_fmm_lists(Tree& t, hipStream_t s) {
     std::vector<int32_t> gc(h.begin() + 5, h.end());
     int32_t* items = A.up<int32_t>(std::max<int64_t>(t.n_u + t.n_w + t.n_x, 1));
     t.u_items = t.w_items = t.x_items = items;
-    hipLaunchKernelGGL(k_uwx, dim3(grid_for(nc, 64)), dim3(64), 0, s, t.cells, nc, t.coll,
+    hipLaunchKernelGGL(k_uwx, dim3(grid_for(nc, 8)), dim3(256), 0, s, t.cells, nc, t.coll,
                        t.cflag, nullptr, nullptr, nullptr, nullptr, nullptr, t.u_off, t.w_off,
                        t.x_off, items, items, items);
     LAUNCH_CHECK();
