@@ -278,7 +278,10 @@ void launch_p2p(const Tree& t, const Targets& tg, int precision, double eps2,
 }
 
 // ---------------------------------------------------------------------
-// direct sum: targets in chunks of 64 per wave, all sources streamed
+// direct sum: a block of 4 waves takes 64 / G targets, and its 4 G lane
+// groups share the sources (wave w the chunks w, w + 4, ... of 64, group g
+// every G-th source of a chunk); the groups are summed by shuffles and
+// through LDS, so no partial result leaves the block.
 // ---------------------------------------------------------------------
 template <typename T>
 __global__ void k_pack_points(const double* __restrict__ x, const double* __restrict__ y,
@@ -289,36 +292,61 @@ __global__ void k_pack_points(const double* __restrict__ x, const double* __rest
     out[i] = typename Vec4<T>::type{(T)x[i], (T)y[i], (T)z[i], m ? (T)m[i] : T(0)};
 }
 
-template <typename T, bool SOFT>
+// Bound by the VALU issue of the pairs.  With one wave per 64 targets over
+// all the sources, N = 30011 ran 469 waves on 1024 SIMDs (1.27 ms, 7.1e11
+// pairs/s); the split keeps every SIMD's wave slots filled down to a few
+// thousand targets (N = 30011: 0.38 ms, 2.4e12 pairs/s).
+template <typename T, int G, bool SOFT>
 __global__ void __launch_bounds__(256)
 k_direct(const typename Vec4<T>::type* __restrict__ src, int64_t ns,
          const typename Vec4<T>::type* __restrict__ tgt, int64_t nt, T eps2,
          T* __restrict__ phi_o, T* __restrict__ ax_o, T* __restrict__ ay_o,
          T* __restrict__ az_o) {
     using V = typename Vec4<T>::type;
+    constexpr int TW = 64 / G;
     __shared__ V shm[4][64];
+    __shared__ V red[4][TW];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t i = ((int64_t)blockIdx.x * 4 + w) * 64 + lane;
-    if (((int64_t)blockIdx.x * 4 + w) * 64 >= nt) return;
-    V me = i < nt ? tgt[i] : V{T(0), T(0), T(0), T(0)};
+    const int g = lane / TW, t = lane % TW;
+    const int64_t i = (int64_t)blockIdx.x * TW + t;
+    const V me = i < nt ? tgt[i] : V{T(0), T(0), T(0), T(0)};
     V* sh = shm[w];
     T phi = T(0), ax = T(0), ay = T(0), az = T(0);
-    for (int64_t base = 0; base < ns; base += 64) {
-        const int64_t k = base + lane;
-        V v = k < ns ? src[k] : V{T(0), T(0), T(0), T(0)};
+    // the next chunk's load is issued before the current chunk's pairs
+    int64_t base = (int64_t)w * 64;
+    V v = base + lane < ns ? src[base + lane] : p2p_pad<T>();
+    for (; base < ns; base += 256) {
         wave_lds_fence();
         sh[lane] = v;
         wave_lds_fence();
-        const int nl = (int)min((int64_t)64, ns - base);
-#pragma unroll 8
-        for (int q = 0; q < nl; ++q)
-            pair<T, SOFT, true>(me.x, me.y, me.z, sh[q], eps2, phi, ax, ay, az);
+        const int64_t k = base + 256 + lane;
+        v = k < ns ? src[k] : p2p_pad<T>();
+        p2p_staged<T, G, SOFT, true>(sh, (int)min((int64_t)64, ns - base), g, me.x, me.y, me.z,
+                                     eps2, phi, ax, ay, az);
     }
-    if (i < nt) {
-        phi_o[i] = phi;
-        ax_o[i] = ax;
-        ay_o[i] = ay;
-        az_o[i] = az;
+#pragma unroll
+    for (int d = TW; d < 64; d <<= 1) {
+        phi += __shfl_xor(phi, d, 64);
+        ax += __shfl_xor(ax, d, 64);
+        ay += __shfl_xor(ay, d, 64);
+        az += __shfl_xor(az, d, 64);
+    }
+    if (lane < TW) red[w][t] = V{phi, ax, ay, az};
+    __syncthreads();
+    if (w == 0 && lane < TW && i < nt) {
+        V a = red[0][t];
+#pragma unroll
+        for (int k = 1; k < 4; ++k) {
+            const V b = red[k][t];
+            a.x += b.x;
+            a.y += b.y;
+            a.z += b.z;
+            a.w += b.w;
+        }
+        phi_o[i] = a.x;
+        ax_o[i] = a.y;
+        ay_o[i] = a.z;
+        az_o[i] = a.w;
     }
 }
 
@@ -338,13 +366,28 @@ static void direct_t(const double* x, const double* y, const double* z, const do
                            tz, (const double*)nullptr, nt, tgt);
         LAUNCH_CHECK();
     }
-    dim3 grid((unsigned)((nt + 255) / 256)), block(256);
-    if (eps2 != 0.0)
-        hipLaunchKernelGGL((k_direct<T, true>), grid, block, 0, s, src, ns, tgt, nt, (T)eps2,
-                           (T*)phi, (T*)ax, (T*)ay, (T*)az);
+    // the widest target tile that still gives each of the 256 CUs 16 blocks
+    // (8 resident at once; 8 more even out the tail)
+    const int64_t tiles = 16 * 256;
+#define DIRECT_LAUNCH(G)                                                                       \
+    {                                                                                          \
+        const dim3 grid((unsigned)((nt + 64 / G - 1) / (64 / G)));                             \
+        if (eps2 != 0.0)                                                                       \
+            hipLaunchKernelGGL((k_direct<T, G, true>), grid, dim3(256), 0, s, src, ns, tgt, nt, \
+                               (T)eps2, (T*)phi, (T*)ax, (T*)ay, (T*)az);                      \
+        else                                                                                   \
+            hipLaunchKernelGGL((k_direct<T, G, false>), grid, dim3(256), 0, s, src, ns, tgt,   \
+                               nt, (T)eps2, (T*)phi, (T*)ax, (T*)ay, (T*)az);                  \
+    }
+    if (nt >= 64 * tiles)
+        DIRECT_LAUNCH(1)
+    else if (nt >= 32 * tiles)
+        DIRECT_LAUNCH(2)
+    else if (nt >= 16 * tiles)
+        DIRECT_LAUNCH(4)
     else
-        hipLaunchKernelGGL((k_direct<T, false>), grid, block, 0, s, src, ns, tgt, nt, (T)eps2,
-                           (T*)phi, (T*)ax, (T*)ay, (T*)az);
+        DIRECT_LAUNCH(8)
+#undef DIRECT_LAUNCH
     LAUNCH_CHECK();
 }
 

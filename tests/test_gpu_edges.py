@@ -53,3 +53,21 @@ def test_list_traversals_deep(kind, leaf):
         for b in range(T.ncells):
             assert np.array_equal(np.sort(git[goff[b]:goff[b + 1]]),
                                   np.sort(it[off[b]:off[b + 1]])), (w, b)
+
+
+# ---------------------------------------------------------------- direct sum
+# FP64: every term is good to a few 2^-53 and at most 257 of one sign are
+# added, so 257 * 2^-53 < 1e-13 bounds phi; the acceleration's terms cancel by
+# less than 10 in a uniform cube.  FP32: coordinates rounded to 2^-25 of the
+# cube against separations above 1e-3 for all but a few pairs.
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-12), ("fp32", 1e-3)])
+@pytest.mark.parametrize("nt,ns", [(1, 1), (7, 64), (9, 257), (64, 63), (65537, 65),
+                                   (131075, 257), (262145, 3)])
+def test_direct_target_tiles(nt, ns, prec, tol):
+    say(f"direct nt={nt} ns={ns} {prec}")
+    x, y, z, m = W.uniform(ns, 51)
+    tx, ty, tz, _ = W.uniform(nt, 52)
+    ref = O.direct_points(x, y, z, m, tx, ty, tz)
+    out = host(H().direct(*to_dev(x, y, z, m), precision=prec, targets=to_dev(tx, ty, tz)))
+    torch.cuda.synchronize()
+    assert_close(out, ref, tol, f"direct {prec}")
