@@ -223,7 +223,7 @@ struct Tree {
     // FMM lists (independent of p and masses)
     bool fmm_lists = false;
     int32_t* coll = nullptr;         // [ncells][27] colleagues, -1 padded
-    int32_t* vsrc = nullptr;         // [ncells][216] V list by slot, -1 empty
+    int32_t* vsrc = nullptr;         // [ncells][216] V list by slot position, -1 empty
     uint8_t* cflag = nullptr;        // [ncells] bit 0: a colleague is a leaf;
                                      // bit 1: so is one of a proper ancestor
     // U, W, X share one item array; offsets are absolute into it
@@ -239,8 +239,10 @@ struct Tree {
     int32_t* m2l_tiles = nullptr;    // per tile: start into m2l_torder, count, octant
     std::vector<int32_t> m2l_tiles_h;  // host copy (the source of the upload)
     int32_t n_m2l_tiles = 0;
+    int32_t m2l_gw = 1;              // tiles per tile group (8: one per octant, or 1)
     uint32_t* m2l_tmask = nullptr;   // per tile: slots with a source (8 words)
-    int32_t* m2l_tpre = nullptr;     // per tile: M2L work items before it (+ total)
+    uint32_t* m2l_gmask = nullptr;   // per tile group: the OR of its tiles' masks
+    int32_t* m2l_gpre = nullptr;     // per tile group: M2L work items before it (+ total)
     size_t mark_lists = 0;
     // treecode lists (bh_theta = kFmmListTheta: built from the FMM lists)
     double bh_theta = -1.0;
@@ -300,6 +302,14 @@ struct PhaseTimer {
 __host__ __device__ constexpr int tri(int n, int m) { return n * (n + 1) / 2 + m; }
 __host__ __device__ constexpr int ntri(int p) { return p * (p + 1) / 2; }
 __host__ __device__ constexpr int round_up(int a, int b) { return (a + b - 1) / b * b; }
+
+// V rows hold their 216 offset slots (slot = 36 x + 6 y + z, a source at
+// offset (x, y, z) - 2 - octant from the target) in this order: position k
+// holds slot 49 k mod 216.  A run of positions then has nearly the same number
+// of slots with a source for every octant (the 27 empty slots around the
+// target lie together in slot order, elsewhere for each octant: up to 8 more
+// than the mean in one run, 2.6 in this order, the least of all multipliers).
+__host__ __device__ constexpr int v_slot_at(int pos) { return pos * 49 % 216; }
 
 // real-layout index of (n, m >= 0, part) with part 0 = Re, 1 = Im
 __host__ __device__ constexpr int ridx(int n, int m, int part) {

@@ -15,7 +15,8 @@
 // target in octant o of its parent sees its V cells at integer offsets
 // d in [-2-o, 3-o]^3 (per axis), 6^3 = 216 slots of which the 27 adjacent
 // ones stay empty, so slot -> offset class is the same for all targets of one
-// octant; the M2L kernel batches targets of one octant.
+// octant; the M2L kernel batches targets of one octant.  Slots are stored,
+// masked and run in the order of v_slot_at.
 //
 // Treecode lists follow the Barnes-Hut acceptance of Sec. 4 per target leaf:
 // a cell C is accepted when l_C < theta * d, d being the distance from C's
@@ -155,11 +156,11 @@ k_vlist(const Cell* __restrict__ cells, int nc, const int32_t* __restrict__ coll
         uint64_t occ[4];     // slots with a source, 64 per word
 #pragma unroll
         for (int s0 = 0; s0 < kSlots; s0 += 64) {
-            const int slot = s0 + lane;
+            const int pos = s0 + lane, slot = v_slot_at(pos);
             const int dx = slot / 36 - 2 - ox, dy = (slot / 6) % 6 - 2 - oy,
                       dz = slot % 6 - 2 - oz;
             const int X = B.ix + dx, Y = B.iy + dy, Z = B.iz + dz;
-            const bool ok = slot < kSlots && max(abs(dx), max(abs(dy), abs(dz))) > 1 &&
+            const bool ok = pos < kSlots && max(abs(dx), max(abs(dy), abs(dz))) > 1 &&
                             X >= 0 && Y >= 0 && Z >= 0;
             const int q = ok ? ((X >> 1) - (B.ix >> 1) + 1) * 9 +
                                    ((Y >> 1) - (B.iy >> 1) + 1) * 3 +
@@ -169,7 +170,7 @@ k_vlist(const Cell* __restrict__ cells, int nc, const int32_t* __restrict__ coll
             const int o = ((X & 1) << 2) | ((Y & 1) << 1) | (Z & 1);
             const int res =
                 ok && ((m >> o) & 1) ? ch + __popc((unsigned)m & ((1u << o) - 1u)) : -1;
-            if (slot < kSlots) out[slot] = res;
+            if (pos < kSlots) out[pos] = res;
             occ[s0 / 64] = __ballot(res >= 0);
             cnt += __popcll(occ[s0 / 64]);
             if (res >= 0) {
@@ -550,14 +551,16 @@ __global__ void k_m2l_keys(const Cell* __restrict__ cells, const uint8_t* __rest
 
 // Per M2L tile: the slots (of 216) in which some target of the tile has a
 // source (the OR of the targets' slot masks, bit j % 32 of word j / 32, 8
-// words, 7 used), and the tile's number of work items, max(1, that many
-// slots).  One wave per tile.
-__global__ void __launch_bounds__(256)
-k_tile_masks(const int32_t* __restrict__ tiles, int ntiles, const int32_t* __restrict__ order,
+// words, 7 used); per tile group (gw consecutive tiles, one block of gw
+// waves) the OR of its tiles' masks and the group's number of work items,
+// max(1, that many slots).
+__global__ void __launch_bounds__(512)
+k_tile_masks(const int32_t* __restrict__ tiles, const int32_t* __restrict__ order,
              const uint32_t* __restrict__ vmask, uint32_t* __restrict__ tmask,
-             int32_t* __restrict__ items) {
-    const int t = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6), lane = threadIdx.x & 63;
-    if (t >= ntiles) return;  // uniform per wave
+             uint32_t* __restrict__ gmask, int32_t* __restrict__ items) {
+    __shared__ uint32_t sm[8][8];
+    const int w = threadIdx.x >> 6, gw = blockDim.x >> 6, lane = threadIdx.x & 63;
+    const int t = blockIdx.x * gw + w;
     const int start = tiles[4 * t], count = tiles[4 * t + 1];
     uint32_t m[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
     for (int i = lane; i < count; i += 64) {
@@ -566,21 +569,29 @@ k_tile_masks(const int32_t* __restrict__ tiles, int ntiles, const int32_t* __res
         m[0] |= a.x, m[1] |= a.y, m[2] |= a.z, m[3] |= a.w;
         m[4] |= b.x, m[5] |= b.y, m[6] |= b.z, m[7] |= b.w;
     }
-    int n = 0;
 #pragma unroll
-    for (int w = 0; w < 8; ++w) {
+    for (int k = 0; k < 8; ++k)
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) m[w] |= __shfl_xor(m[w], off, 64);
-        n += __popc(m[w]);
-    }
+        for (int off = 32; off > 0; off >>= 1) m[k] |= __shfl_xor(m[k], off, 64);
     if (lane < 8) {
         uint32_t v = m[0];
 #pragma unroll
-        for (int w = 1; w < 8; ++w)
-            if (lane == w) v = m[w];
+        for (int k = 1; k < 8; ++k)
+            if (lane == k) v = m[k];
         tmask[8 * t + lane] = v;
+        sm[w][lane] = v;
     }
-    if (lane == 0) items[t] = max(1, n);
+    __syncthreads();
+    if (w == 0) {
+        uint32_t v = 0u;
+        if (lane < 8)
+            for (int k = 0; k < gw; ++k) v |= sm[k][lane];
+        if (lane < 8) gmask[8 * blockIdx.x + lane] = v;
+        int n = __popc(v);
+#pragma unroll
+        for (int off = 4; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
+        if (lane == 0) items[blockIdx.x] = max(1, n);
+    }
 }
 
 void build_fmm_lists(Tree& t, hipStream_t s) {
@@ -670,43 +681,66 @@ void build_fmm_lists(Tree& t, hipStream_t s) {
     }
     // M2L tiles: runs of up to 256 targets of one octant, levels mixed (the
     // scaled operators do not depend on the level and every source is read
-    // by index), so only the last tile of an octant is partly filled.  Within
-    // an octant the targets come by the sides of their V-list sources, so
-    // that a tile's targets mostly lack the same slots (a tile skips a slot
-    // only when none of its targets has a source there).  Tiles are listed
-    // as (k, octant) for the k-th tile of each octant: the eight tiles of one
-    // k cover about the same stretch of the order and read nearly the same
-    // source expansions.
+    // by index).  Within an octant the targets come by the sides of their
+    // V-list sources, so that a tile's targets mostly lack the same slots (a
+    // tile skips a slot only when none of its targets has a source there).
+    // Tiles are listed as (k, octant) for the k-th tile of each octant: the
+    // eight tiles of one k cover about the same parents, and in one slot read
+    // the same source expansions (a slot is an offset from the parent).  When
+    // every octant makes about as many tiles, each is cut into the same number
+    // of equal tiles, and the eight tiles of one k form a tile group, which
+    // eight blocks of one XCD run in step (k_m2l_mma).  Otherwise each tile is
+    // its own group: in planar or other lopsided sets a group would leave blocks
+    // without a tile, more than the 1 in 8 that the shared reads could repay;
+    // and below 32 groups (one for each team of the 256 CUs) a team's run of
+    // slots is shorter than a group and its octants' shares of it differ by a
+    // few percent.  Measured, groups of 8 against 1, FP32 unless noted: 2^20
+    // uniform, p = 10 (19 groups) 0.71 against 0.69 ms; 2^22 Plummer, p = 8
+    // (248 groups) 4.8 against 5.1 ms; 2^22 uniform, p = 12, BF16x3 (146
+    // groups) 7.7 against 8.0 ms.
     std::vector<int32_t>& tiles = t.m2l_tiles_h;
     tiles.clear();
     int ocount[8] = {0}, ostart[9] = {0};
-    for (int o = 0; o < 8; ++o)
+    int ntile[8], ktile = 0, ntot = 0;
+    for (int o = 0; o < 8; ++o) {
         for (int l = 0; l <= HFMM_KEY_LEVELS + 1; ++l) ocount[o] += gc[l * 8 + o];
-    for (int o = 0; o < 8; ++o) ostart[o + 1] = ostart[o] + ocount[o];
-    const int kmax = *std::max_element(ocount, ocount + 8);
-    for (int k = 0; k < kmax; k += 256)
+        ostart[o + 1] = ostart[o] + ocount[o];
+        ntile[o] = (ocount[o] + 255) / 256;
+        ktile = std::max(ktile, ntile[o]);
+        ntot += ntile[o];
+    }
+    t.m2l_gw = ktile >= 32 && 7 * 8 * ktile <= 8 * ntot ? 8 : 1;
+    for (int k = 0; k < ktile; ++k)
         for (int o = 0; o < 8; ++o) {
-            if (k >= ocount[o]) continue;
-            tiles.push_back(ostart[o] + k);
-            tiles.push_back(std::min(256, ocount[o] - k));
+            int first = k * 256, count = std::min(256, ocount[o] - first);
+            if (t.m2l_gw == 8) {
+                first = (int)((int64_t)ocount[o] * k / ktile);
+                count = (int)((int64_t)ocount[o] * (k + 1) / ktile) - first;
+            } else if (count <= 0) {
+                continue;
+            }
+            tiles.push_back(ostart[o] + first);
+            tiles.push_back(count);
             tiles.push_back(o);
             tiles.push_back(0);
         }
     t.n_m2l_tiles = (int32_t)(tiles.size() / 4);
+    const int ngroup = t.n_m2l_tiles / t.m2l_gw;
     t.m2l_tiles = A.up<int32_t>(std::max<size_t>(tiles.size(), 4));
     if (!tiles.empty())  // (the host copy lives as long as the tree)
         HIP_TRY(hipMemcpyAsync(t.m2l_tiles, tiles.data(), sizeof(int32_t) * tiles.size(),
                                hipMemcpyHostToDevice, s));
-    // the M2L's work items: slot masks of the tiles and their prefix sums
+    // the M2L's work items: slot masks of the tiles and groups and the
+    // groups' prefix sums
     t.m2l_tmask = A.up<uint32_t>((size_t)std::max(t.n_m2l_tiles, 1) * 8);
-    t.m2l_tpre = A.up<int32_t>((size_t)t.n_m2l_tiles + 1);
-    if (t.n_m2l_tiles > 0) {
-        int32_t* titems = A.down<int32_t>(t.n_m2l_tiles);
-        hipLaunchKernelGGL(k_tile_masks, dim3(grid_for((int64_t)t.n_m2l_tiles * 64, 256)),
-                           dim3(256), 0, s, t.m2l_tiles, t.n_m2l_tiles, t.m2l_torder, vmask,
-                           t.m2l_tmask, titems);
+    t.m2l_gmask = A.up<uint32_t>((size_t)std::max(ngroup, 1) * 8);
+    t.m2l_gpre = A.up<int32_t>((size_t)ngroup + 1);
+    if (ngroup > 0) {
+        int32_t* gitems = A.down<int32_t>(ngroup);
+        hipLaunchKernelGGL(k_tile_masks, dim3(ngroup), dim3(64 * t.m2l_gw), 0, s, t.m2l_tiles,
+                           t.m2l_torder, vmask, t.m2l_tmask, t.m2l_gmask, gitems);
         LAUNCH_CHECK();
-        scan_exclusive_i32(titems, t.m2l_tpre, t.n_m2l_tiles, A, s);
+        scan_exclusive_i32(gitems, t.m2l_gpre, ngroup, A, s);
     }
     A.release_temps();
     t.fmm_lists = true;

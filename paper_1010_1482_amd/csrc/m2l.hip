@@ -45,8 +45,9 @@ k_m2l_valu(const Cell* __restrict__ cells, int c0, int c1, const int32_t* __rest
     const int ox = B.ix & 1, oy = B.iy & 1, oz = B.iz & 1;
     T acc[4] = {T(0), T(0), T(0), T(0)};
     const int64_t per = (int64_t)P * P;
-    for (int slot = 0; slot < 216; ++slot) {
-        const int src = vsrc[(int64_t)c * 216 + slot];
+    for (int pos = 0; pos < 216; ++pos) {
+        const int slot = v_slot_at(pos);
+        const int src = vsrc[(int64_t)c * 216 + pos];
         if (src < 0) continue;
         const int dx = slot / 36 - 2 - ox, dy = (slot / 6) % 6 - 2 - oy, dz = slot % 6 - 2 - oz;
         const int cls = (dx + 3) * 49 + (dy + 3) * 7 + (dz + 3);
@@ -165,16 +166,22 @@ __global__ void k_pack_lp(const Cell* __restrict__ cells, const double* __restri
 
 // ---------------------------------------------------------------------
 // Matrix-core M2L.  Block = 8 waves, tile = up to 256 targets of one
-// octant (levels mixed), 32 per wave (two column blocks of 16).  The work
-// items are the (tile, slot) pairs in which some target of the tile has a
-// source, tile by tile (a tile without any counts as one item, which writes
-// zeros); tpre[t] is the number of items before tile t.  Block b takes items
-// [b W / NB, (b + 1) W / NB) of the W items, so every block has the same
-// share of the products.  The consecutive items of one tile in one block
-// are a segment; segment k of a tile (k-th block that touches it) writes
-// partial result k, and the tile's last segment writes zeros to the partial
-// results after its own; the downward pass sums them (deterministic, no
-// atomics).
+// octant (levels mixed), 32 per wave (two column blocks of 16).  gw tiles
+// form a group (8: the k-th tile of every octant, which cover the same
+// parents; or 1).  The work items are the (group, slot) pairs in which some
+// target of the group has a source, group by group (a group without any
+// counts as one item, which writes zeros); gpre[t] is the number of items
+// before group t.  The blocks come in teams of gw: team b takes items
+// [b W / NB, (b + 1) W / NB) of the W items, so every team has the same
+// share of the products, and its block o runs them for tile o of the group
+// (skipping the slots its own tile lacks).  A team's blocks run on one XCD
+// and start together, and in one slot the eight octants read the same source
+// rows (a slot is an offset from the parent), so that a row comes from beyond
+// the XCD's L2 once and not eight times.  The consecutive items of one group
+// in one team are a segment; segment k of a group (k-th team that touches
+// it) writes partial result k, and the group's last segment writes zeros to
+// the partial results after its own; the downward pass sums them
+// (deterministic, no atomics).
 //
 // Both operands travel in 16-byte chunks: chunk 4 q + g of a row holds the
 // contraction elements that lane group g feeds to step q.  For FP32 a chunk
@@ -287,64 +294,72 @@ __device__ inline uint32_t m2l_rank_range(uint32_t m, int base, int lo, int hi) 
     return keep;
 }
 
-// This block's range of work items and the tile of its first item (the
-// items and blocks are described at k_m2l_mma).  Workgroups are handed to
-// the 8 XCDs round-robin; they are renumbered so that each XCD (own L2)
-// runs one contiguous range of blocks, i.e. of items: the blocks resident
-// on an XCD then share tiles and source expansions.
+// This block's range of work items and the group of its first item (the
+// items and teams are described at k_m2l_mma).  Workgroups are handed to
+// the 8 XCDs round-robin: with gw = 8, workgroups x, x + 8, ..., x + 56 of
+// each run of 64 are a team (all on XCD x); with gw = 1 each XCD (own L2)
+// runs one contiguous range of blocks, i.e. of items.  A workgroup past the
+// last team gets no items.
 struct M2lItems {
-    int b, item, iend, tile;
+    int b, o, item, iend, group;
     int64_t W;
 };
-__device__ inline M2lItems m2l_items(const int32_t* __restrict__ tpre, int ntiles) {
+__device__ inline M2lItems m2l_items(const int32_t* __restrict__ gpre, int ngroups, int gw,
+                                     int nb) {
     M2lItems it;
-    const int nb = gridDim.x, lin = blockIdx.x;
-    const int xcd = lin & 7, q8 = nb >> 3, r8 = nb & 7;
-    it.b = xcd * q8 + min(xcd, r8) + (lin >> 3);
-    it.W = tpre[ntiles];
+    const int lin = blockIdx.x;
+    if (gw == 8) {
+        it.b = (lin >> 6) * 8 + (lin & 7);
+        it.o = (lin >> 3) & 7;
+    } else {
+        const int xcd = lin & 7, q8 = nb >> 3, r8 = nb & 7;
+        it.b = xcd * q8 + min(xcd, r8) + (lin >> 3);
+        it.o = 0;
+    }
+    it.W = gpre[ngroups];
     it.item = (int)((int64_t)it.b * it.W / nb);
-    it.iend = (int)((int64_t)(it.b + 1) * it.W / nb);
-    // the last tile with tpre[tile] <= item: a 64-way search, every lane
-    // probing one point of [lo, hi) per round (tpre[lo] <= item < tpre[hi])
+    it.iend = it.b < nb ? (int)((int64_t)(it.b + 1) * it.W / nb) : it.item;
+    // the last group with gpre[group] <= item: a 64-way search, every lane
+    // probing one point of [lo, hi) per round (gpre[lo] <= item < gpre[hi])
     const int lane = threadIdx.x & 63;
-    int lo = 0, hi = ntiles;
+    int lo = 0, hi = ngroups;
     while (hi - lo > 1) {
         const int step = (hi - lo + 63) / 64;
         const int idx = lo + lane * step;
-        const bool le = idx < hi && tpre[idx] <= it.item;
+        const bool le = idx < hi && gpre[idx] <= it.item;
         const int k = __popcll(__ballot(le));  // lanes 0 .. k-1 (lane 0 always)
         hi = min(hi, lo + k * step);
         lo = lo + (k - 1) * step;
     }
-    it.tile = lo;
+    it.group = lo;
     return it;
 }
 
-// The segment of tile it.tile that starts at it.item: its partial-result
-// number (blocks before this one that hold items of the tile), whether it
-// is the tile's last, and its slots (the tile's slots with a source whose
-// ranks fall in the segment) as a mask, the same in every lane.  Moves
-// it.item to the segment's end.
+// The segment of group it.group that starts at it.item: its partial-result
+// number (teams before this one that hold items of the group), whether it
+// is the group's last, and this block's slots (the group's slots whose ranks
+// fall in the segment and in which its own tile has a source) as a mask, the
+// same in every lane.  Moves it.item to the segment's end.
 __device__ inline void m2l_segment(const uint32_t* __restrict__ tmask,
-                                   const int32_t* __restrict__ tpre, M2lItems& it, int& part,
-                                   bool& last, uint32_t (&mw)[7]) {
-    const int nb = gridDim.x;
-    const int p0 = tpre[it.tile], p1 = tpre[it.tile + 1];
+                                   const uint32_t* __restrict__ gmask,
+                                   const int32_t* __restrict__ gpre, int tile, int nb,
+                                   M2lItems& it, int& part, bool& last, uint32_t (&mw)[7]) {
+    const int p0 = gpre[it.group], p1 = gpre[it.group + 1];
     const int seg_end = min(it.iend, p1);
     part = it.b - (int)((((int64_t)p0 + 1) * nb - 1) / it.W);
     last = seg_end == p1;
     int base = 0;
 #pragma unroll
     for (int w = 0; w < 7; ++w) {
-        const uint32_t m = tmask[8 * it.tile + w];
+        const uint32_t m = gmask[8 * it.group + w];
         mw[w] = __builtin_amdgcn_readfirstlane(
-            m2l_rank_range(m, base, it.item - p0, seg_end - p0));
+            m2l_rank_range(m, base, it.item - p0, seg_end - p0) & tmask[8 * tile + w]);
         base += __popc(m);
     }
     it.item = seg_end;
 }
 
-// first slot >= j of the mask, else 216
+// first slot position >= j of the mask, else 216
 __device__ inline int m2l_next_slot(const uint32_t (&mw)[7], int j) {
 #pragma unroll
     for (int w = 0; w < 7; ++w) {
@@ -365,7 +380,8 @@ typedef const __attribute__((address_space(1))) void* gbl_ptr;
 template <int RB, int KQ, int CB, bool DB, class Op, int LASTS = Op::S, int LASTR = 16>
 __global__ void __launch_bounds__(1024 / CB)
 k_m2l_mma(const int32_t* __restrict__ tiles, const uint32_t* __restrict__ tmask,
-          const int32_t* __restrict__ tpre, int ntiles, int nparts,
+          const uint32_t* __restrict__ gmask, const int32_t* __restrict__ gpre, int ngroups,
+          int gw, int nb, int nparts,
           const int32_t* __restrict__ order, const int32_t* __restrict__ vsrc,
           const typename Op::E* __restrict__ Mhi, const typename Op::E* __restrict__ Mlo,
           int ncells, const typename Op::E* __restrict__ Thi,
@@ -378,16 +394,16 @@ k_m2l_mma(const int32_t* __restrict__ tiles, const uint32_t* __restrict__ tmask,
     constexpr int NW = 16 / CB;       // waves per block (CB column blocks each)
     __shared__ u32x4 sT[NS * NT];
     __shared__ u32x4 sT2[DB ? NS * NT : 1];
-    M2lItems it = m2l_items(tpre, ntiles);
+    M2lItems it = m2l_items(gpre, ngroups, gw, nb);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g = lane >> 4, col = lane & 15;
     constexpr int s0 = 0, ns = 216;
-    for (; it.item < it.iend; ++it.tile) {
-        const int tile = it.tile;
+    for (; it.item < it.iend; ++it.group) {
+        const int tile = it.group * gw + it.o;
         int part;
         bool last_seg;
         uint32_t mw[7];
-        m2l_segment(tmask, tpre, it, part, last_seg, mw);
+        m2l_segment(tmask, gmask, gpre, tile, nb, it, part, last_seg, mw);
         const int start = tiles[4 * tile], count = tiles[4 * tile + 1], oct = tiles[4 * tile + 2];
         const int ox = (oct >> 2) & 1, oy = (oct >> 1) & 1, oz = oct & 1;
         auto next_slot = [&](int j) -> int { return m2l_next_slot(mw, j); };
@@ -415,7 +431,7 @@ k_m2l_mma(const int32_t* __restrict__ tiles, const uint32_t* __restrict__ tmask,
         // operator of relative slot jj -> LDS buffer (each wave copies every
         // NW-th 1-KiB chunk with direct global-to-LDS loads)
         auto stage = [&](u32x4* buf, int jj) {
-            const int slot = s0 + jj;
+            const int slot = v_slot_at(s0 + jj);
             const int dx = slot / 36 - 2 - ox, dy = (slot / 6) % 6 - 2 - oy, dz = slot % 6 - 2 - oz;
             const int cls = (dx + 3) * 49 + (dy + 3) * 7 + (dz + 3);
             const u32x4* th = (const u32x4*)Thi + (int64_t)cls * NT;
@@ -551,7 +567,7 @@ k_m2l_mma(const int32_t* __restrict__ tiles, const uint32_t* __restrict__ tmask,
 #pragma unroll
             for (int u = 0; u < (NQ > 0 ? NQ : 1); ++u) accq[cb][u] = floatx4{0.f, 0.f, 0.f, 0.f};
         auto load_op = [&](int jj, u32x4 (&r)[NPW][NS]) {
-            const int slot = s0 + jj;
+            const int slot = v_slot_at(s0 + jj);
             const int dx = slot / 36 - 2 - ox, dy = (slot / 6) % 6 - 2 - oy, dz = slot % 6 - 2 - oz;
             const int cls = (dx + 3) * 49 + (dy + 3) * 7 + (dz + 3);
             const u32x4* th = (const u32x4*)Thi + (int64_t)cls * NT;
@@ -786,19 +802,19 @@ k_m2l_mma(const int32_t* __restrict__ tiles, const uint32_t* __restrict__ tmask,
 }
 
 // Many partial results (small problems spread over many blocks): instead of
-// clearing the partial results its segments did not write, each tile's
-// segments 1 .. S-1 are added to partial result 0, in order (S = the blocks
-// that held the tile's items, from the same item ranges as the M2L launch of
-// nb blocks).  Block (t, y) takes elements 4 y .. 4 y + 3 of the rows of tile
+// clearing the partial results its segments did not write, each group's
+// segments 1 .. S-1 are added to partial result 0, in order (S = the teams
+// that held the group's items, from the same item ranges as the M2L launch of
+// nb teams).  Block (t, y) takes elements 4 y .. 4 y + 3 of the rows of tile
 // t's targets, one thread per target, eight partial results in flight.
 template <typename TO>
 __global__ void __launch_bounds__(256)
-k_m2l_sum_parts(const int32_t* __restrict__ tiles, const int32_t* __restrict__ tpre, int nb,
-                const int32_t* __restrict__ order, TO* __restrict__ out, int64_t part_stride,
-                int ldo) {
+k_m2l_sum_parts(const int32_t* __restrict__ tiles, const int32_t* __restrict__ gpre, int gw,
+                int nb, const int32_t* __restrict__ order, TO* __restrict__ out,
+                int64_t part_stride, int ldo) {
     const int t = blockIdx.x;
-    const int64_t W = tpre[gridDim.x];
-    const int p0 = tpre[t], p1 = tpre[t + 1];
+    const int64_t W = gpre[gridDim.x / gw];
+    const int p0 = gpre[t / gw], p1 = gpre[t / gw + 1];
     const int b0 = (int)((((int64_t)p0 + 1) * nb - 1) / W);
     const int b1 = (int)((((int64_t)p1) * nb - 1) / W);  // block of item p1 - 1
     const int segs = b1 - b0 + 1;
@@ -984,16 +1000,16 @@ void prepare_rot_ops(Tree& t, int p, int precision, hipStream_t s) {
     t.mark_ops = t.arena.lo;
 }
 
-// Blocks and partial results of the matrix-core M2L.  The W work items
-// (tile slots with a source, at least one per tile) number at least n_v / c,
-// c the largest tile, since a slot of a tile covers at most c V pairs;
-// blocks get at least m = floor(W_lb / NB) items each, so a tile's at most
-// 216 items fall into at most 1 + ceil(215 / m) blocks, the number of partial
-// results.  One block per CU (two when the operator buffers take at most
-// 80 KiB of LDS), fewer when the partial results would exceed max_parts.
-// Returns the number of partial results (0 without M2L targets).
+// Teams and partial results of the matrix-core M2L.  The W work items
+// (group slots with a source, at least one per group) number at least
+// n_v / (c gw), c the largest tile, since a slot of a group covers at most
+// c gw V pairs; the NB teams get at least m = floor(W_lb / NB) items each, so
+// a group's at most 216 items fall into at most 1 + ceil(215 / m) teams, the
+// number of partial results.  One block per CU (two when the operator buffers
+// take at most 80 KiB of LDS), fewer when the partial results would exceed
+// max_parts.  Returns the number of partial results (0 without M2L targets).
 int m2l_plan(const Tree& t, int p, int precision, int max_parts, int& nb) {
-    const int ntiles = t.n_m2l_tiles;
+    const int ntiles = t.n_m2l_tiles, gw = t.m2l_gw, ngroups = ntiles / gw;
     nb = 0;
     if (t.depth < 2 || ntiles == 0) return 0;
     int RB, KQ, ld;
@@ -1002,8 +1018,9 @@ int m2l_plan(const Tree& t, int p, int precision, int max_parts, int& nb) {
                        (is_x3(precision) ? 2 : 1) * RB * KQ;
     int cmax = 1;
     for (int k = 0; k < ntiles; ++k) cmax = std::max(cmax, t.m2l_tiles_h[4 * k + 1]);
-    const int64_t w_lb = std::max<int64_t>(ntiles, (t.n_v + cmax - 1) / cmax);
-    nb = m2l_cus(t.device) * (lds_kb <= 80 ? 2 : 1);
+    const int64_t w_lb =
+        std::max<int64_t>(ngroups, (t.n_v + (int64_t)cmax * gw - 1) / ((int64_t)cmax * gw));
+    nb = std::max(1, m2l_cus(t.device) * (lds_kb <= 80 ? 2 : 1) / gw);
     if (max_parts <= 1) {
         nb = 1;
     } else {
@@ -1049,7 +1066,8 @@ int run_m2l(Tree& t, int p, int precision, void* out, int64_t& part_stride, int 
         return 0;
     }
     part_stride = (int64_t)t.ncells * t.ldm;
-    dim3 grid(nb), block(1024 / kM2LCB);
+    const int gw = t.m2l_gw, ngroups = ntiles / gw;
+    dim3 grid(gw == 8 ? (nb + 7) / 8 * 64 : nb), block(1024 / kM2LCB);
     // up to kDirectParts partial results go to the L2L epilogue as they are
     // (the segments clear the ones they do not write); more are first summed
     // into the first
@@ -1058,7 +1076,8 @@ int run_m2l(Tree& t, int p, int precision, void* out, int64_t& part_stride, int 
     auto finish = [&](auto* o) -> int {
         if (fill) return parts;
         hipLaunchKernelGGL(k_m2l_sum_parts, dim3(ntiles, 4 * RB), dim3(256), 0, s,
-                           t.m2l_tiles, t.m2l_tpre, nb, t.m2l_torder, o, part_stride, 16 * RB);
+                           t.m2l_tiles, t.m2l_gpre, t.m2l_gw, nb, t.m2l_torder, o, part_stride,
+                           16 * RB);
         LAUNCH_CHECK();
         return 1;
     };
@@ -1075,7 +1094,7 @@ int run_m2l(Tree& t, int p, int precision, void* out, int64_t& part_stride, int 
         constexpr int K = ((PP) * (PP) + 7) / 8;                                              \
         constexpr int LS = ((PP) * (PP) - 8 * (K - 1) + 3) / 4;                               \
         hipLaunchKernelGGL((k_m2l_mma<R, K, kM2LCB, m2l_double_buffer(R, K, 1), OpF64, LS>),  \
-                           grid, block, 0, s, t.m2l_tiles, t.m2l_tmask, t.m2l_tpre, ntiles,  \
+                           grid, block, 0, s, t.m2l_tiles, t.m2l_tmask, t.m2l_gmask, t.m2l_gpre, ngroups, gw, nb, \
                            parts, t.m2l_torder, t.vsrc, (const double*)Mk,                    \
                            (const double*)nullptr, t.ncells, (const double*)t.T,              \
                            (const double*)nullptr, (double*)out, part_stride, fill);          \
@@ -1112,7 +1131,7 @@ int run_m2l(Tree& t, int p, int precision, void* out, int64_t& part_stride, int 
         constexpr int LR = (PP) * (PP) - 16 * (R - 1);                                       \
         hipLaunchKernelGGL((k_m2l_mma<R, R, kM2LCB, m2l_double_buffer(R, R, 1), OpF32, LS,   \
                                       LR>),                                                  \
-                           grid, block, 0, s, t.m2l_tiles, t.m2l_tmask, t.m2l_tpre, ntiles, \
+                           grid, block, 0, s, t.m2l_tiles, t.m2l_tmask, t.m2l_gmask, t.m2l_gpre, ngroups, gw, nb, \
                            parts, t.m2l_torder, t.vsrc, (const float*)Mk,                    \
                            (const float*)nullptr, t.ncells, (const float*)t.T,               \
                            (const float*)nullptr, (float*)out, part_stride, fill);          \
@@ -1146,11 +1165,11 @@ int run_m2l(Tree& t, int p, int precision, void* out, int64_t& part_stride, int 
 #define LP_CASE(R)                                                                             \
     if (x3)                                                                                    \
         hipLaunchKernelGGL((k_m2l_mma<R, (R + 1) / 2, kM2LCB, m2l_double_buffer(R, (R + 1) / 2, 2), OpLow<__bf16, true>>), grid, block, 0, s,    \
-                           t.m2l_tiles, t.m2l_tmask, t.m2l_tpre, ntiles, parts, t.m2l_torder,    \
+                           t.m2l_tiles, t.m2l_tmask, t.m2l_gmask, t.m2l_gpre, ngroups, gw, nb, parts, t.m2l_torder,    \
                            t.vsrc, mh, ml, t.ncells, th, tl, (float*)out, part_stride, fill);   \
     else                                                                                       \
         hipLaunchKernelGGL((k_m2l_mma<R, (R + 1) / 2, kM2LCB, m2l_double_buffer(R, (R + 1) / 2, 1), OpLow<__bf16, false>>), grid, block, 0, s,   \
-                           t.m2l_tiles, t.m2l_tmask, t.m2l_tpre, ntiles, parts, t.m2l_torder,    \
+                           t.m2l_tiles, t.m2l_tmask, t.m2l_gmask, t.m2l_gpre, ngroups, gw, nb, parts, t.m2l_torder,    \
                            t.vsrc, mh, ml, t.ncells, th, tl, (float*)out, part_stride, fill);
         HFMM_DISPATCH_RB(RB, LP_CASE);
 #undef LP_CASE
@@ -1167,11 +1186,11 @@ int run_m2l(Tree& t, int p, int precision, void* out, int64_t& part_stride, int 
 #define LP_CASE(R)                                                                             \
     if (x3)                                                                                    \
         hipLaunchKernelGGL((k_m2l_mma<R, (R + 1) / 2, kM2LCB, m2l_double_buffer(R, (R + 1) / 2, 2), OpLow<_Float16, true>>), grid, block, 0, s,  \
-                           t.m2l_tiles, t.m2l_tmask, t.m2l_tpre, ntiles, parts, t.m2l_torder,    \
+                           t.m2l_tiles, t.m2l_tmask, t.m2l_gmask, t.m2l_gpre, ngroups, gw, nb, parts, t.m2l_torder,    \
                            t.vsrc, mh, ml, t.ncells, th, tl, (float*)out, part_stride, fill);   \
     else                                                                                       \
         hipLaunchKernelGGL((k_m2l_mma<R, (R + 1) / 2, kM2LCB, m2l_double_buffer(R, (R + 1) / 2, 1), OpLow<_Float16, false>>), grid, block, 0, s, \
-                           t.m2l_tiles, t.m2l_tmask, t.m2l_tpre, ntiles, parts, t.m2l_torder,    \
+                           t.m2l_tiles, t.m2l_tmask, t.m2l_gmask, t.m2l_gpre, ngroups, gw, nb, parts, t.m2l_torder,    \
                            t.vsrc, mh, ml, t.ncells, th, tl, (float*)out, part_stride, fill);
         HFMM_DISPATCH_RB(RB, LP_CASE);
 #undef LP_CASE

@@ -243,8 +243,9 @@ k_m2l_rot(const int32_t* __restrict__ tiles, const int32_t* __restrict__ torder,
     T acc[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) acc[u] = T(0);
-    for (int slot = 0; slot < 216; ++slot) {
-        const int src = c >= 0 ? vsrc[(int64_t)c * 216 + slot] : -1;
+    for (int pos = 0; pos < 216; ++pos) {
+        const int slot = v_slot_at(pos);
+        const int src = c >= 0 ? vsrc[(int64_t)c * 216 + pos] : -1;
         // the block's barrier before the tables are overwritten, and whether
         // any of its targets has a source in this slot
         if (!__syncthreads_or(src >= 0)) continue;
