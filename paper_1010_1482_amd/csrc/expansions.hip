@@ -3,6 +3,7 @@
 // normalisation for inspection.  See common.hpp for the basis.
 #include "common.hpp"
 #include "expansions.hpp"
+#include "m2l_table.hpp"
 
 #include <algorithm>
 
@@ -905,101 +906,8 @@ __global__ void k_to_float(const double* __restrict__ a, int64_t n, float* __res
 }
 
 // ---------------------------------------------------------------------
-// M2L operator of one offset class from Eq. 4.  With the identity of Sec. 5.2,
-// Y_N^M / (A_N^M rho^{N+1}) = (N-|M|)! P_N^|M|(cos a) e^{iM b} / rho^{N+1},
-// and the change to the device basis (Lb = L / A_j^k, Mb = A_n^m M), the
-// factors A_n^m A_j^k of Eq. 4 cancel and the complex coefficient of
-// M_n^m in L_j^k becomes
-//   c(j,k,n,m) = i^{|k-m|-|k|-|m|} (-1)^j (N-|M|)! P_N^|M| e^{iM b} / rho^{N+1}
-// with N = j + n, M = m - k, (rho, a, b) the spherical coordinates of
-// c_target - c_source in cell units (offsets are source minus target, so the
-// vector is -d).  Conjugate symmetry of M folds m and -m into real entries.
+// M2L operator tables
 // ---------------------------------------------------------------------
-__device__ inline double factorial_d(int n) {
-    double f = 1.0;
-    for (int i = 2; i <= n; ++i) f *= (double)i;
-    return f;
-}
-
-// real-layout index -> (n, m, part)
-__device__ inline void rdecode(int r, int& n, int& m, int& part) {
-    n = 0;
-    while ((n + 1) * (n + 1) <= r) ++n;
-    int o = r - n * n;
-    if (o == 0) {
-        m = 0;
-        part = 0;
-    } else {
-        m = (o + 1) / 2;
-        part = (o + 1) % 2;
-    }
-}
-
-// One block per offset class (343 blocks, 27 of them adjacent offsets that
-// stay zero).  The block tabulates, for this class, the Sec. 5.2 quantity
-// (N-|M|)! P_N^|M|(cos a) / rho^{N+1} for N <= 2p-2 (Eqs. 7-9) and
-// cos(M b), sin(M b) in LDS, then threads fill the real entries.  Writes the
-// FP64 layout T64[cls][ri][ro] and/or the FP32 matrix-core layout
-// Tsw[cls][rb][q][lane][4] with T[16 rb + (lane & 15)][16 q + 4 (lane >> 4) + r].
-constexpr int kNmax = 2 * HFMM_MAX_P - 1;
-
-// LDS table of one offset class; returns false for the 27 adjacent offsets
-__device__ inline bool m2l_class_table(int p, int cls, double (*pt)[kNmax],
-                                       double (*cs)[2]) {
-    const int ND = 2 * p - 1;
-    const int dx = cls / 49 - 3, dy = (cls / 7) % 7 - 3, dz = cls % 7 - 3;
-    const bool far = max(abs(dx), max(abs(dy), abs(dz))) >= 2;
-    if (far && (int)threadIdx.x < ND) {
-        const int a = threadIdx.x;  // order |M|
-        const double vx = -dx, vy = -dy, vz = -dz;
-        const double rxy = sqrt(vx * vx + vy * vy);
-        const double rho = sqrt(vx * vx + vy * vy + vz * vz);
-        const double x = vz / rho, sn = rxy / rho;
-        const double beta = (vx == 0.0 && vy == 0.0) ? 0.0 : atan2(vy, vx);
-        cs[a][0] = cos(a * beta);
-        cs[a][1] = sin(a * beta);
-        double pmm = 1.0;  // Eq. 8
-        for (int i = 1; i <= a; ++i) pmm *= -(double)(2 * i - 1) * sn;
-        double rinv = 1.0 / rho, rpow = rinv;  // 1 / rho^{N+1}
-        for (int i = 0; i < a; ++i) rpow *= rinv;
-        double pm1 = 0.0, pc = pmm, fct = 1.0;  // P_{N-1}, P_N, (N - a)!
-        for (int N = a; N < ND; ++N) {
-            pt[N][a] = fct * pc * rpow;
-            const double pn = N == a ? x * (2 * a + 1) * pmm                                 // Eq. 9
-                                     : (x * (2 * N + 1) * pc - (N + a) * pm1) / (N - a + 1);  // Eq. 7
-            pm1 = pc;
-            pc = pn;
-            fct *= (double)(N - a + 1);
-            rpow *= rinv;
-        }
-    }
-    __syncthreads();
-    return far;
-}
-
-// real entry (row ro, column ri) of the class operator from its table:
-// c(j,k,n,+-m) = i^{|k-m|-|k|-|m|} (-1)^j pt[j+n][|m-k|] e^{i (m-k) b}
-__device__ inline double m2l_entry(int ro, int ri, const double (*pt)[kNmax],
-                                   const double (*cs)[2]) {
-    int j, k, po, n, m, pi;
-    rdecode(ro, j, k, po);
-    rdecode(ri, n, m, pi);
-    auto coef = [&](int mm) {
-        const int M = mm - k, aM = M < 0 ? -M : M;
-        const int ev = abs(k - mm) - abs(k) - abs(mm);
-        const double sg = (((ev / 2) & 1) ? -1.0 : 1.0) * ((j & 1) ? -1.0 : 1.0);
-        const double v = sg * pt[j + n][aM];
-        return make_double2(v * cs[aM][0], v * (M < 0 ? -cs[aM][1] : cs[aM][1]));
-    };
-    if (m == 0) {
-        double2 c0 = coef(0);
-        return pi == 0 ? (po == 0 ? c0.x : c0.y) : 0.0;
-    }
-    double2 cp = coef(m), cm = coef(-m);
-    if (po == 0) return pi == 0 ? cp.x + cm.x : -(cp.y - cm.y);
-    return pi == 0 ? cp.y + cm.y : cp.x - cm.x;
-}
-
 // gridDim.y blocks per offset class (343 classes, 27 of them adjacent
 // offsets that stay zero).  Each block tabulates, for its class, the Sec. 5.2
 // quantity (N-|M|)! P_N^|M|(cos a) / rho^{N+1} for N <= 2p-2 (Eqs. 7-9) and
@@ -1014,18 +922,17 @@ k_m2l_ops(int p, int layout, void* __restrict__ T, int RB, int KQ) {
     // chunks (E = 4, KS = 16); 2: FP64 matrix-core chunks (E = 2, KS = 8).
     // The r-major order puts the padding of the last block into whole
     // products, which the kernel skips.
-    __shared__ double pt[kNmax][kNmax];
-    __shared__ double cs[kNmax][2];
+    __shared__ M2lClassTable tab;
     const int P = p * p;
     const int cls = blockIdx.x;
-    const bool far = m2l_class_table(p, cls, pt, cs);
+    const bool far = tab.fill(p, cls);
     const int64_t per = (int64_t)P * P;
     const int64_t step = (int64_t)gridDim.y * blockDim.x;
     const int64_t first = (int64_t)blockIdx.y * blockDim.x + threadIdx.x;
     if (layout == 0) {
         for (int64_t e = first; e < per; e += step) {
             const int ri = (int)(e / P), ro = (int)(e % P);
-            ((double*)T)[(int64_t)cls * per + e] = far ? m2l_entry(ro, ri, pt, cs) : 0.0;
+            ((double*)T)[(int64_t)cls * per + e] = far ? tab.entry(ro, ri) : 0.0;
         }
         return;
     }
@@ -1036,18 +943,12 @@ k_m2l_ops(int p, int layout, void* __restrict__ T, int RB, int KQ) {
         const int64_t u = o / E;
         const int lane = (int)(u % 64), q = (int)((u / 64) % KQ), rb = (int)(u / (64 * KQ));
         const int ro = 16 * rb + (lane & 15), ri = KS * q + 4 * r + (lane >> 4);
-        const double val = (far && ro < P && ri < P) ? m2l_entry(ro, ri, pt, cs) : 0.0;
+        const double val = (far && ro < P && ri < P) ? tab.entry(ro, ri) : 0.0;
         if (layout == 1)
             ((float*)T)[(int64_t)cls * tot + o] = (float)val;
         else
             ((double*)T)[(int64_t)cls * tot + o] = val;
     }
-}
-
-__device__ inline int mu_exp_d(int n) {  // floor(log2((sqrt3/2)^n / n!))
-    double v = 1.0;
-    for (int i = 1; i <= n; ++i) v *= 0.8660254037844386 / (double)i;
-    return ilogb(v);
 }
 
 // Low-precision operators.  pass 0: bexp[j] = max exponent of T_{jn} 2^{mu_n}
@@ -1058,13 +959,12 @@ template <typename T16>
 __global__ void __launch_bounds__(256)
 k_m2l_ops_lp(int p, int pass, int RB, int KQ, int32_t* __restrict__ bexp,
              T16* __restrict__ hi, T16* __restrict__ lo) {
-    __shared__ double pt[kNmax][kNmax];
-    __shared__ double cs[kNmax][2];
-    __shared__ int bmax[kNmax];  // pass 0: block maximum per output degree
+    __shared__ M2lClassTable tab;
+    __shared__ int bmax[HFMM_MAX_P];  // pass 0: block maximum per output degree
     const int P = p * p;
     const int cls = blockIdx.x;
-    if (threadIdx.x < kNmax) bmax[threadIdx.x] = INT_MIN;
-    const bool far = m2l_class_table(p, cls, pt, cs);
+    if (threadIdx.x < HFMM_MAX_P) bmax[threadIdx.x] = INT_MIN;
+    const bool far = tab.fill(p, cls);
     const int R = 16 * RB, K = 32 * KQ;
     const int64_t per = (int64_t)R * K;
     for (int64_t e = threadIdx.x; e < per; e += blockDim.x) {
@@ -1072,16 +972,15 @@ k_m2l_ops_lp(int p, int pass, int RB, int KQ, int32_t* __restrict__ bexp,
         double val = 0.0;
         int j = 0, n = 0;
         if (far && ro < P && ri < P) {
-            val = m2l_entry(ro, ri, pt, cs);
-            j = 0;
-            while ((j + 1) * (j + 1) <= ro) ++j;
-            while ((n + 1) * (n + 1) <= ri) ++n;
+            val = tab.entry(ro, ri);
+            j = tab.dec[ro] & 255;
+            n = tab.dec[ri] & 255;
         }
         if (pass == 0) {
-            if (val != 0.0) atomicMax(&bmax[j], ilogb(fabs(val)) + mu_exp_d(n));
+            if (val != 0.0) atomicMax(&bmax[j], ilogb(fabs(val)) + m2l_mu(n));
             continue;
         }
-        double t = val == 0.0 ? 0.0 : ldexp(val, mu_exp_d(n) - (bexp[j] + 1));
+        double t = val == 0.0 ? 0.0 : ldexp(val, m2l_mu(n) - (bexp[j] + 1));
         const int rb = ro / 16, il = ro % 16;
         const int q = ri / 32, g = (ri % 32) / 8, jj = ri % 8;
         const int64_t idx = ((((int64_t)cls * RB + rb) * KQ + q) * 64 + g * 16 + il) * 8 + jj;
@@ -1129,6 +1028,12 @@ __global__ void k_pack(const double* __restrict__ M, int ldm, int ncells, int P,
     const int k = blk * 4 * NR + 4 * (w % NR) + w / NR;
     double v = (c < ncells && k < P) ? M[(int64_t)c * ldm + k] : 0.0;
     out[gid] = (TO)v;
+}
+
+__device__ inline double factorial_d(int n) {
+    double f = 1.0;
+    for (int i = 2; i <= n; ++i) f *= (double)i;
+    return f;
 }
 
 // device basis -> the paper's normalisation:

@@ -40,4 +40,13 @@ int run_m2l(Tree& t, int p, int precision, void* out, int64_t& part_stride, int 
             int32_t* levexp, hipStream_t s);
 int m2l_plan(const Tree& t, int p, int precision, int max_parts, int& nb);
 
+// FP32 M2L on split BF16 operands (m2l_split.hip)
+bool m2l_uses_split(int p, int precision);
+int split_row_floats(int p);
+size_t split_ops_bytes(int p);
+void run_split_ops(int p, void* T, hipStream_t s);
+void run_split_pack(const Tree& t, int p, float* Mk, hipStream_t s);
+void run_m2l_split(const Tree& t, int p, const float* Mk, dim3 grid, int nb, int parts,
+                   float* out, int64_t part_stride, int fill, hipStream_t s);
+
 }  // namespace hfmm

@@ -17,6 +17,8 @@
 // arrive with 16-byte loads.
 #include "common.hpp"
 #include "expansions.hpp"
+#include "m2l_items.hpp"
+#include "m2l_table.hpp"
 
 #include <algorithm>
 #include <atomic>
@@ -105,18 +107,6 @@ struct LowP<_Float16> {
     }
 };
 
-__device__ inline int mu_exp(int n) {
-    double v = 1.0;
-    for (int i = 1; i <= n; ++i) v *= 0.8660254037844386 / (double)i;
-    return ilogb(v);
-}
-
-__device__ inline int degree_of(int r) {
-    int n = 0;
-    while ((n + 1) * (n + 1) <= r) ++n;
-    return n;
-}
-
 // Per level: the largest exponent of the scaled coefficients
 // Mt_k 2^{-mu_n}, over every cell and every coefficient of the level (not
 // only the monopole: with masses of both signs a near-neutral cell has a
@@ -134,7 +124,7 @@ __global__ void k_level_exp(const Cell* __restrict__ cells, int nc, const double
         const double* row = M + (int64_t)c * ldm;
         int e = INT_MIN;
         for (int n = 0; n < p; ++n) {
-            const int mu = mu_exp(n);
+            const int mu = m2l_mu(n);
             for (int k = n * n; k < (n + 1) * (n + 1); ++k) {
                 const double v = fabs(row[k]);
                 if (v > 0.0) e = max(e, ilogb(v) - mu);
@@ -157,7 +147,7 @@ __global__ void k_pack_lp(const Cell* __restrict__ cells, const double* __restri
     double v = 0.0;
     if (c < ncells && k < P) {
         const int e = level_exp(levexp, cells[c].level);
-        v = ldexp(M[(int64_t)c * ldm + k], -mu_exp(degree_of(k)) - (e + 1));
+        v = ldexp(M[(int64_t)c * ldm + k], -m2l_mu(degree_of(k)) - (e + 1));
     }
     const T16 h = (T16)(float)v;
     hi[gid] = h;
@@ -280,96 +270,6 @@ struct OpF64 {
         for (int r = 0; r < 4; ++r) o[16 * rb + 4 * r + g] = c[r];
     }
 };
-
-// bits of m whose rank among the set bits, counted from `base`, lies in
-// [lo, hi)
-__device__ inline uint32_t m2l_rank_range(uint32_t m, int base, int lo, int hi) {
-    for (int k = base; m && k < lo; ++k) m &= m - 1u;  // drop ranks below lo
-    uint32_t keep = 0u;
-    for (int k = max(base, lo); m && k < hi; ++k) {
-        const uint32_t low = m & (0u - m);
-        keep |= low;
-        m ^= low;
-    }
-    return keep;
-}
-
-// This block's range of work items and the group of its first item (the
-// items and teams are described at k_m2l_mma).  Workgroups are handed to
-// the 8 XCDs round-robin: with gw = 8, workgroups x, x + 8, ..., x + 56 of
-// each run of 64 are a team (all on XCD x); with gw = 1 each XCD (own L2)
-// runs one contiguous range of blocks, i.e. of items.  A workgroup past the
-// last team gets no items.
-struct M2lItems {
-    int b, o, item, iend, group;
-    int64_t W;
-};
-__device__ inline M2lItems m2l_items(const int32_t* __restrict__ gpre, int ngroups, int gw,
-                                     int nb) {
-    M2lItems it;
-    const int lin = blockIdx.x;
-    if (gw == 8) {
-        it.b = (lin >> 6) * 8 + (lin & 7);
-        it.o = (lin >> 3) & 7;
-    } else {
-        const int xcd = lin & 7, q8 = nb >> 3, r8 = nb & 7;
-        it.b = xcd * q8 + min(xcd, r8) + (lin >> 3);
-        it.o = 0;
-    }
-    it.W = gpre[ngroups];
-    it.item = (int)((int64_t)it.b * it.W / nb);
-    it.iend = it.b < nb ? (int)((int64_t)(it.b + 1) * it.W / nb) : it.item;
-    // the last group with gpre[group] <= item: a 64-way search, every lane
-    // probing one point of [lo, hi) per round (gpre[lo] <= item < gpre[hi])
-    const int lane = threadIdx.x & 63;
-    int lo = 0, hi = ngroups;
-    while (hi - lo > 1) {
-        const int step = (hi - lo + 63) / 64;
-        const int idx = lo + lane * step;
-        const bool le = idx < hi && gpre[idx] <= it.item;
-        const int k = __popcll(__ballot(le));  // lanes 0 .. k-1 (lane 0 always)
-        hi = min(hi, lo + k * step);
-        lo = lo + (k - 1) * step;
-    }
-    it.group = lo;
-    return it;
-}
-
-// The segment of group it.group that starts at it.item: its partial-result
-// number (teams before this one that hold items of the group), whether it
-// is the group's last, and this block's slots (the group's slots whose ranks
-// fall in the segment and in which its own tile has a source) as a mask, the
-// same in every lane.  Moves it.item to the segment's end.
-__device__ inline void m2l_segment(const uint32_t* __restrict__ tmask,
-                                   const uint32_t* __restrict__ gmask,
-                                   const int32_t* __restrict__ gpre, int tile, int nb,
-                                   M2lItems& it, int& part, bool& last, uint32_t (&mw)[7]) {
-    const int p0 = gpre[it.group], p1 = gpre[it.group + 1];
-    const int seg_end = min(it.iend, p1);
-    part = it.b - (int)((((int64_t)p0 + 1) * nb - 1) / it.W);
-    last = seg_end == p1;
-    int base = 0;
-#pragma unroll
-    for (int w = 0; w < 7; ++w) {
-        const uint32_t m = gmask[8 * it.group + w];
-        mw[w] = __builtin_amdgcn_readfirstlane(
-            m2l_rank_range(m, base, it.item - p0, seg_end - p0) & tmask[8 * tile + w]);
-        base += __popc(m);
-    }
-    it.item = seg_end;
-}
-
-// first slot position >= j of the mask, else 216
-__device__ inline int m2l_next_slot(const uint32_t (&mw)[7], int j) {
-#pragma unroll
-    for (int w = 0; w < 7; ++w) {
-        if (j < 32 * w + 32) {
-            const uint32_t bb = j > 32 * w ? mw[w] & (~0u << (j - 32 * w)) : mw[w];
-            if (bb) return 32 * w + __builtin_ctz(bb);
-        }
-    }
-    return 216;
-}
 
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef const __attribute__((address_space(1))) void* gbl_ptr;
@@ -884,6 +784,9 @@ void m2l_layout(int p, int precision, int& RB, int& KQ, int& ld) {
     if (!m2l_uses_mfma(p, precision)) {
         KQ = 0;
         ld = 16 * RB;
+    } else if (m2l_uses_split(p, precision)) {
+        KQ = 0;
+        ld = split_row_floats(p);
     } else if (is_lowp(precision)) {
         KQ = (P + 31) / 32;
         ld = 32 * KQ;
@@ -902,29 +805,12 @@ size_t m2l_ops_bytes(int p, int precision) {
     const int P = p * p;
     if (!m2l_uses_mfma(p, precision))
         return (size_t)343 * P * P * (precision == HFMM_FP64 ? sizeof(double) : sizeof(float));
+    if (m2l_uses_split(p, precision)) return split_ops_bytes(p);
     if (precision == HFMM_FP64) return (size_t)343 * RB * KQ * 64 * 16;
     if (is_lowp(precision))
         return (size_t)343 * RB * KQ * 64 * 16 * (is_x3(precision) ? 2 : 1) + 256;
     return (size_t)343 * RB * KQ * 64 * 4 * sizeof(float);
 }
-
-#define HFMM_DISPATCH_P13(P_, F) \
-    switch (P_) {                \
-        case 1: F(1); break;     \
-        case 2: F(2); break;     \
-        case 3: F(3); break;     \
-        case 4: F(4); break;     \
-        case 5: F(5); break;     \
-        case 6: F(6); break;     \
-        case 7: F(7); break;     \
-        case 8: F(8); break;     \
-        case 9: F(9); break;     \
-        case 10: F(10); break;   \
-        case 11: F(11); break;   \
-        case 12: F(12); break;   \
-        case 13: F(13); break;   \
-        default: throw Status{HFMM_E_UNSUPPORTED}; \
-    }
 
 #define HFMM_DISPATCH_RB(R, F) \
     switch (R) {               \
@@ -969,6 +855,8 @@ void prepare_m2l_ops(Tree& t, int p, int precision, hipStream_t s) {
         hipLaunchKernelGGL((k_cast_ops<float>), dim3(grid_for(nn, 256)), dim3(256), 0, s, tmp,
                            nn, (float*)t.T);
         LAUNCH_CHECK();
+    } else if (m2l_uses_split(p, precision)) {
+        run_split_ops(p, t.T, s);
     } else if (is_lowp(precision)) {
         const size_t half = (size_t)343 * RB * KQ * 64 * 8;  // 16-bit elements per operand set
         char* hi = (char*)t.T;
@@ -1006,7 +894,7 @@ void prepare_rot_ops(Tree& t, int p, int precision, hipStream_t s) {
 // c gw V pairs; the NB teams get at least m = floor(W_lb / NB) items each, so
 // a group's at most 216 items fall into at most 1 + ceil(215 / m) teams, the
 // number of partial results.  One block per CU (two when the operator buffers
-// take at most 80 KiB of LDS), fewer when the partial results would exceed
+// take at most 80 KiB of LDS; the split kernel's registers allow one), fewer when the partial results would exceed
 // max_parts.  Returns the number of partial results (0 without M2L targets).
 int m2l_plan(const Tree& t, int p, int precision, int max_parts, int& nb) {
     const int ntiles = t.n_m2l_tiles, gw = t.m2l_gw, ngroups = ntiles / gw;
@@ -1016,11 +904,12 @@ int m2l_plan(const Tree& t, int p, int precision, int max_parts, int& nb) {
     m2l_layout(p, precision, RB, KQ, ld);
     const int lds_kb = (m2l_double_buffer(RB, KQ, is_x3(precision) ? 2 : 1) ? 2 : 1) *
                        (is_x3(precision) ? 2 : 1) * RB * KQ;
+    const int per_cu = !m2l_uses_split(p, precision) && lds_kb <= 80 ? 2 : 1;
     int cmax = 1;
     for (int k = 0; k < ntiles; ++k) cmax = std::max(cmax, t.m2l_tiles_h[4 * k + 1]);
     const int64_t w_lb =
         std::max<int64_t>(ngroups, (t.n_v + (int64_t)cmax * gw - 1) / ((int64_t)cmax * gw));
-    nb = std::max(1, m2l_cus(t.device) * (lds_kb <= 80 ? 2 : 1) / gw);
+    nb = std::max(1, m2l_cus(t.device) * per_cu / gw);
     if (max_parts <= 1) {
         nb = 1;
     } else {
@@ -1117,6 +1006,16 @@ int run_m2l(Tree& t, int p, int precision, void* out, int64_t& part_stride, int 
         LAUNCH_CHECK();
         return finish((double*)out);
     }
+    if (m2l_uses_split(p, precision)) {
+        float* Mk = A.down<float>((size_t)(t.ncells + 1) * ld);
+        {
+            PhaseTimer pp(t, PH_M2L_PREP, s);
+            run_split_pack(t, p, Mk, s);
+        }
+        PhaseTimer pt(t, PH_M2L, s);
+        run_m2l_split(t, p, Mk, grid, nb, parts, (float*)out, part_stride, fill, s);
+        return finish((float*)out);
+    }
     if (!is_lowp(precision)) {
         float* Mk = A.down<float>((size_t)(t.ncells + 1) * ld);
         {
@@ -1125,18 +1024,31 @@ int run_m2l(Tree& t, int p, int precision, void* out, int64_t& part_stride, int 
         }
         PhaseTimer pt(t, PH_M2L, s);
 #define MFMA_CASE(PP)                                                                        \
-    {                                                                                        \
+    case PP: {                                                                               \
         constexpr int R = ((PP) * (PP) + 15) / 16;                                           \
         constexpr int LS = ((PP) * (PP) - 16 * (R - 1) + 3) / 4;                             \
         constexpr int LR = (PP) * (PP) - 16 * (R - 1);                                       \
         hipLaunchKernelGGL((k_m2l_mma<R, R, kM2LCB, m2l_double_buffer(R, R, 1), OpF32, LS,   \
                                       LR>),                                                  \
-                           grid, block, 0, s, t.m2l_tiles, t.m2l_tmask, t.m2l_gmask, t.m2l_gpre, ngroups, gw, nb, \
-                           parts, t.m2l_torder, t.vsrc, (const float*)Mk,                    \
-                           (const float*)nullptr, t.ncells, (const float*)t.T,               \
-                           (const float*)nullptr, (float*)out, part_stride, fill);          \
+                           grid, block, 0, s, t.m2l_tiles, t.m2l_tmask, t.m2l_gmask,         \
+                           t.m2l_gpre, ngroups, gw, nb, parts, t.m2l_torder, t.vsrc,         \
+                           (const float*)Mk, (const float*)nullptr, t.ncells,                \
+                           (const float*)t.T, (const float*)nullptr, (float*)out,            \
+                           part_stride, fill);                                               \
+        break;                                                                               \
     }
-        HFMM_DISPATCH_P13(p, MFMA_CASE);
+        switch (p) {  // the other orders run above
+            MFMA_CASE(1)
+            MFMA_CASE(2)
+            MFMA_CASE(3)
+            MFMA_CASE(4)
+            MFMA_CASE(5)
+            MFMA_CASE(6)
+            MFMA_CASE(7)
+            MFMA_CASE(12)
+            MFMA_CASE(13)
+            default: throw Status{HFMM_E_UNSUPPORTED};
+        }
 #undef MFMA_CASE
         LAUNCH_CHECK();
         return finish((float*)out);
@@ -1164,11 +1076,11 @@ int run_m2l(Tree& t, int p, int precision, void* out, int64_t& part_stride, int 
         const __bf16* tl = x3 ? th + half : nullptr;
 #define LP_CASE(R)                                                                             \
     if (x3)                                                                                    \
-        hipLaunchKernelGGL((k_m2l_mma<R, (R + 1) / 2, kM2LCB, m2l_double_buffer(R, (R + 1) / 2, 2), OpLow<__bf16, true>>), grid, block, 0, s,    \
+        hipLaunchKernelGGL((k_m2l_mma<R, (R + 1) / 2, kM2LCB, m2l_double_buffer(R, (R + 1) / 2, 2), OpLow<__bf16, true>>), grid, block, 0, s,  \
                            t.m2l_tiles, t.m2l_tmask, t.m2l_gmask, t.m2l_gpre, ngroups, gw, nb, parts, t.m2l_torder,    \
                            t.vsrc, mh, ml, t.ncells, th, tl, (float*)out, part_stride, fill);   \
     else                                                                                       \
-        hipLaunchKernelGGL((k_m2l_mma<R, (R + 1) / 2, kM2LCB, m2l_double_buffer(R, (R + 1) / 2, 1), OpLow<__bf16, false>>), grid, block, 0, s,   \
+        hipLaunchKernelGGL((k_m2l_mma<R, (R + 1) / 2, kM2LCB, m2l_double_buffer(R, (R + 1) / 2, 1), OpLow<__bf16, false>>), grid, block, 0, s, \
                            t.m2l_tiles, t.m2l_tmask, t.m2l_gmask, t.m2l_gpre, ngroups, gw, nb, parts, t.m2l_torder,    \
                            t.vsrc, mh, ml, t.ncells, th, tl, (float*)out, part_stride, fill);
         HFMM_DISPATCH_RB(RB, LP_CASE);

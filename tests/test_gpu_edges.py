@@ -71,3 +71,23 @@ def test_direct_target_tiles(nt, ns, prec, tol):
     out = host(H().direct(*to_dev(x, y, z, m), precision=prec, targets=to_dev(tx, ty, tz)))
     torch.cuda.synchronize()
     assert_close(out, ref, tol, f"direct {prec}")
+
+
+# ---------------------------------------------------------------- FP32 M2L
+# FP32 against the FP64 evaluation of the same approximation: the bar of the
+# other FP32 tests.  Small leaves give many cells: 32 and more 256-target tiles
+# per octant (tile groups); the flat layer fills four octants (no groups).
+@pytest.mark.parametrize("kind,n,leaf,p", [("uniform", 5000, 16, 9), ("uniform", 150000, 2, 8),
+                                           ("plummer", 150000, 2, 11), ("layer", 60000, 4, 10)])
+def test_fp32_m2l_split_orders_and_tile_groups(kind, n, leaf, p):
+    x, y, z, m = W.make("uniform" if kind == "layer" else kind, n, 61)
+    if kind == "layer":
+        z = 0.25 + 0.0 * z
+    tg = W.sample_targets(n, 64, 62)
+    ref = O.fmm(x, y, z, m, p, leaf, targets=tg)
+    say(f"fmm fp32 {kind} n={n} leaf={leaf} p={p}")
+    out = [o[tg] for o in host(H().solve(*to_dev(x, y, z, m), p=p, method="fmm",
+                                         precision="fp32", leaf_max=leaf))]
+    if kind == "layer":  # the field lies in the plane: its third component is rounding
+        out, ref = out[:3], ref[:3]
+    assert_close(out, ref, 1e-5, "vs oracle fmm")
