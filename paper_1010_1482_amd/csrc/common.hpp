@@ -367,21 +367,17 @@ __device__ __forceinline__ void wave_lds_fence() {
 // The owner lane of each of `width` consecutive slots of a packed sequence:
 // lane j holds a run [off, off + cnt) of it; the runs are in lane order.  The
 // lane whose run starts in the window (or covers its first slot) marks that
-// slot in own[], then a running maximum over the lanes fills the rest.
-// Returns the owner of slot pb + lane (meaningful for slots < total).
+// slot in own[]; a slot's owner is the last mark at or before it, found in the
+// ballot of the marks.  Returns the owner of slot pb + lane (meaningful for
+// slots < total).
 __device__ __forceinline__ int wave_run_owner(int* own, int off, int cnt, int pb, int width,
                                               int lane) {
     wave_lds_fence();
     own[lane] = -1;
     if (cnt > 0 && off < pb + width && off + cnt > pb) own[max(off - pb, 0)] = lane;
     wave_lds_fence();
-    int o = own[lane];
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int u = __shfl_up(o, d, 64);
-        if (lane >= d) o = max(o, u);
-    }
-    return o;
+    const uint64_t marks = __ballot(own[lane] >= 0) & (~0ull >> (63 - lane));
+    return own[marks ? 63 - __clzll((long long)marks) : 0];
 }
 
 // Exponent of the low-precision M2L operand scale of one level; the

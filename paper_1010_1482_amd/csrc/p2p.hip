@@ -4,14 +4,14 @@
 // reciprocal square root (Listing 1 of Sec. 5.1 plus the potential), pairs
 // at r^2 == 0 skipped.  The paper gives each target cell a thread block and
 // pads the targets to the block size (Secs. 3 and 5.1); leaves here hold up
-// to ~32 particles (clustered data: ~10 on average), so one 64-lane wave
-// takes one target leaf and, when the leaf has at most 32 (16, 8) targets,
-// splits the sources over 2 (4, 8) lane groups that are summed with
-// cross-lane shuffles at the end.  The sources of consecutive list cells are
-// packed into chunks of 64 (x, y, z, m) records in LDS, so a chunk is full
-// however few particles each cell holds; the target leaf itself, whose
-// coincident points need the r^2 == 0 test, is taken on its own.  Each wave
-// owns its LDS slice, so there is no block-wide barrier.
+// to 64 particles (about 32 on average, clustered data about 10), so one
+// 64-lane wave takes one target leaf: TW lanes hold TPL targets each, and the
+// 64 / TW lane groups share the sources and are summed with cross-lane
+// shuffles at the end.  The sources of consecutive list cells are packed into
+// chunks of 64 (x, y, z, m) records in LDS, so a chunk is full however few
+// particles each cell holds; the target leaf itself, whose coincident points
+// need the r^2 == 0 test, is taken on its own.  Each wave owns its LDS slice,
+// so there is no block-wide barrier.
 #include "common.hpp"
 #include "expansions.hpp"
 
@@ -46,18 +46,28 @@ __device__ __forceinline__ void pair(T xi, T yi, T zi, const typename Vec4<T>::t
     az += dz * sc;
 }
 
-// Sum over the sources staged in sh[0, nl): lane layout TW = 64 / G
-// targets, lane = g * TW + t, group g takes sources g, g + G, ...  Entries
-// past nl up to the next multiple of G are padding (mass 0, far away).
-template <typename T, int G, bool SOFT, bool ZERO>
-__device__ __forceinline__ void p2p_staged(const typename Vec4<T>::type* sh, int nl, int g,
-                                           T xi, T yi, T zi, T eps2, T& phi, T& ax, T& ay,
-                                           T& az) {
+// The targets of a lane: positions and sums.
+template <typename T, int TPL>
+struct LaneTargets {
+    T x[TPL], y[TPL], z[TPL];
+    T phi[TPL], ax[TPL], ay[TPL], az[TPL];
+};
+
+// Sum over the sources staged in sh[0, nl): lane = g * TW + t, group g of the
+// G = 64 / TW takes sources g, g + G, ..., each read once for the lane's TPL
+// targets.  Entries past nl up to the next multiple of G are padding (mass 0,
+// far away).
+template <typename T, int G, int TPL, bool SOFT, bool ZERO>
+__device__ __forceinline__ void p2p_staged(const typename Vec4<T>::type* sh, int nl, int g, T eps2,
+                                           LaneTargets<T, TPL>& me) {
     const int steps = (nl + G - 1) / G;
-#pragma unroll 8
+#pragma unroll(TPL > 2 ? 4 : 8)
     for (int q = 0; q < steps; ++q) {
         const typename Vec4<T>::type s = sh[q * G + g];
-        pair<T, SOFT, ZERO>(xi, yi, zi, s, eps2, phi, ax, ay, az);
+#pragma unroll
+        for (int k = 0; k < TPL; ++k)
+            pair<T, SOFT, ZERO>(me.x[k], me.y[k], me.z[k], s, eps2, me.phi[k], me.ax[k], me.ay[k],
+                                me.az[k]);
     }
 }
 
@@ -70,12 +80,11 @@ __device__ __forceinline__ typename Vec4<T>::type p2p_pad() {
 // The target box's own leaf as a source (coincident points possible): the
 // sources of cell c against targets me.  In FP32 both are relative to the
 // same centre (the box is the leaf), so no offset is added.
-template <typename T, int G, bool SOFT>
+template <typename T, int G, int TPL, bool SOFT>
 __device__ __forceinline__ void p2p_self(const Cell& c, const typename Vec4<T>::type* __restrict__ P,
-                                         typename Vec4<T>::type* sh, T xi, T yi, T zi, T eps2,
-                                         T& phi, T& ax, T& ay, T& az) {
-    constexpr int TW = 64 / G;
-    const int lane = threadIdx.x & 63, g = lane / TW;
+                                         typename Vec4<T>::type* sh, T eps2,
+                                         LaneTargets<T, TPL>& me) {
+    const int lane = threadIdx.x & 63, g = lane / (64 / G);
     const int end = c.first + c.count;
     for (int base = c.first; base < end; base += 64) {
         const int k = base + lane;
@@ -83,8 +92,7 @@ __device__ __forceinline__ void p2p_self(const Cell& c, const typename Vec4<T>::
         wave_lds_fence();
         sh[lane] = v;
         wave_lds_fence();
-        p2p_staged<T, G, SOFT, true>(sh, min(64, end - base), g, xi, yi, zi, eps2, phi, ax, ay,
-                                     az);
+        p2p_staged<T, G, TPL, SOFT, true>(sh, min(64, end - base), g, eps2, me);
     }
 }
 
@@ -93,17 +101,16 @@ __device__ __forceinline__ void p2p_self(const Cell& c, const typename Vec4<T>::
 // between its centre and the target leaf's centre, formed in FP64; a scan
 // over the counts places the batch's particles in one sequence, which is
 // staged 64 at a time.
-template <typename T, int G, bool SOFT>
+template <typename T, int G, int TPL, bool SOFT>
 __device__ __forceinline__ void p2p_packed(const Cell* __restrict__ cells, int self,
                                            const int32_t* __restrict__ items, int e0, int e1,
                                            const typename Vec4<T>::type* __restrict__ P,
                                            typename Vec4<T>::type* sh, int* own,
-                                           const Root& root, const double cb[3], T xi, T yi,
-                                           T zi, T eps2, T& phi, T& ax, T& ay, T& az) {
+                                           const Root& root, const double cb[3], T eps2,
+                                           LaneTargets<T, TPL>& me) {
     using V = typename Vec4<T>::type;
-    constexpr int TW = 64 / G;
     constexpr bool REL = sizeof(T) == 4;
-    const int lane = threadIdx.x & 63, g = lane / TW;
+    const int lane = threadIdx.x & 63, g = lane / (64 / G);
     for (int eb = e0; eb < e1; eb += 64) {
         int first = 0, cnt = 0;
         T ox = T(0), oy = T(0), oz = T(0);
@@ -124,6 +131,7 @@ __device__ __forceinline__ void p2p_packed(const Cell* __restrict__ cells, int s
         }
         int tot;
         const int off = wave_excl_scan(cnt, lane, tot);
+        tot = __builtin_amdgcn_readfirstlane(tot);
         // lane's source of the run [pb, pb + 64) of the batch's particles;
         // the next run's load is issued before the current run's pairs
         auto fetch = [&](int pb, V& v, T& sx, T& sy, T& sz) {
@@ -154,8 +162,7 @@ __device__ __forceinline__ void p2p_packed(const Cell* __restrict__ cells, int s
             wave_lds_fence();
             sh[lane] = cur;
             wave_lds_fence();
-            p2p_staged<T, G, SOFT, false>(sh, min(64, tot - pb), g, xi, yi, zi, eps2, phi, ax,
-                                          ay, az);
+            p2p_staged<T, G, TPL, SOFT, false>(sh, min(64, tot - pb), g, eps2, me);
         }
     }
 }
@@ -163,7 +170,7 @@ __device__ __forceinline__ void p2p_packed(const Cell* __restrict__ cells, int s
 // The targets of one box against the list cells items[e0, e1) (the box's
 // own leaf, when it is in the list, summed on its own with the r^2 == 0
 // test).  TP: the sorted targets, P: the sorted sources.
-template <typename T, typename O, int G, bool SOFT>
+template <typename T, int TW, int TPL, bool SOFT>
 __device__ __forceinline__ void p2p_box(const TBox& bx, bool in_list, const Root& root,
                                         const Cell* __restrict__ cells,
                                         const int32_t* __restrict__ items, int e0, int e1,
@@ -172,59 +179,76 @@ __device__ __forceinline__ void p2p_box(const TBox& bx, bool in_list, const Root
                                         typename Vec4<T>::type* sh, int* own,
                                         const T* __restrict__ far, int64_t n,
                                         const int32_t* __restrict__ perm, T eps2,
-                                        O* __restrict__ phi_o, O* __restrict__ ax_o,
-                                        O* __restrict__ ay_o, O* __restrict__ az_o) {
+                                        T* __restrict__ phi_o, T* __restrict__ ax_o,
+                                        T* __restrict__ ay_o, T* __restrict__ az_o) {
     using V = typename Vec4<T>::type;
-    constexpr int TW = 64 / G;
+    constexpr int G = 64 / TW;
+    static_assert(TW <= 16, "the sums of the lane groups end in the lanes' 16-lane rows");
     const int lane = threadIdx.x & 63;
     const int t = lane % TW;
     double cb[3];
     cell_centre(root, box_cell(bx), cb);
     Cell own_leaf;
     if (in_list) own_leaf = cells[bx.leaf];
-    for (int c0 = 0; c0 < bx.count; c0 += TW) {
-        const int s = bx.first + c0 + t;
-        const bool ok = c0 + t < bx.count;
-        V me = ok ? TP[s] : V{T(0), T(0), T(0), T(0)};
-        T phi = T(0), ax = T(0), ay = T(0), az = T(0);
-        if (in_list)
-            p2p_self<T, G, SOFT>(own_leaf, P, sh, me.x, me.y, me.z, eps2, phi, ax, ay, az);
-        p2p_packed<T, G, SOFT>(cells, bx.leaf, items, e0, e1, P, sh, own, root, cb, me.x, me.y,
-                               me.z, eps2, phi, ax, ay, az);
+    for (int c0 = 0; c0 < bx.count; c0 += TW * TPL) {
+        LaneTargets<T, TPL> me;
 #pragma unroll
-        for (int d = TW; d < 64; d <<= 1) {
-            phi += __shfl_xor(phi, d, 64);
-            ax += __shfl_xor(ax, d, 64);
-            ay += __shfl_xor(ay, d, 64);
-            az += __shfl_xor(az, d, 64);
+        for (int k = 0; k < TPL; ++k) {
+            const int i = c0 + k * TW + t;
+            const V q = i < bx.count ? TP[bx.first + i] : V{T(0), T(0), T(0), T(0)};
+            me.x[k] = q.x;
+            me.y[k] = q.y;
+            me.z[k] = q.z;
+            me.phi[k] = me.ax[k] = me.ay[k] = me.az[k] = T(0);
         }
-        if (ok && lane < TW) {
-            const int64_t oi = perm[s];
-            if (far) {
-                phi += far[s];
-                ax += far[n + s];
-                ay += far[2 * n + s];
-                az += far[3 * n + s];
+        if (in_list) p2p_self<T, G, TPL, SOFT>(own_leaf, P, sh, eps2, me);
+        p2p_packed<T, G, TPL, SOFT>(cells, bx.leaf, items, e0, e1, P, sh, own, root, cb, eps2, me);
+        // sum of the G lane groups: the two halves of the wave take two of the
+        // four sums each, their 16-lane rows one each (row 0 phi, 1 ax, 2 ay,
+        // 3 az), and the groups left inside a row add theirs
+        const bool up = lane & 32, odd = lane & 16;
+        const int row = lane >> 4;
+        T* __restrict__ o = row == 0 ? phi_o : row == 1 ? ax_o : row == 2 ? ay_o : az_o;
+#pragma unroll
+        for (int k = 0; k < TPL; ++k) {
+            const T a = (up ? me.ay[k] : me.phi[k]) + __shfl_xor(up ? me.phi[k] : me.ay[k], 32, 64);
+            const T b = (up ? me.az[k] : me.ax[k]) + __shfl_xor(up ? me.ax[k] : me.az[k], 32, 64);
+            T v = (odd ? b : a) + __shfl_xor(odd ? a : b, 16, 64);
+#pragma unroll
+            for (int d = TW; d < 16; d <<= 1) v += __shfl_xor(v, d, 64);
+            const int i = c0 + k * TW + t;
+            if (i < bx.count && (lane & 15) < TW) {
+                const int s = bx.first + i;
+                if (far) v += far[row * n + s];
+                o[perm[s]] = v;
             }
-            phi_o[oi] = (O)phi;
-            ax_o[oi] = (O)ax;
-            ay_o[oi] = (O)ay;
-            az_o[oi] = (O)az;
         }
     }
 }
 
-// One wave per target box; sources from the box's CSR list row.
-template <typename T, typename O, bool SOFT>
-__global__ void __launch_bounds__(256, 8)
+// One wave per target box; sources from the box's CSR list row.  Bound by the
+// VALU issue of the pairs (14.4 instructions each).  The split of the lanes
+// (TW of 4, 8 or 16, the TPL that covers the box) leaves at most TW - 1 of
+// TW * TPL target slots empty: with one target per lane and TW = 64 beyond 32
+// targets, half of the leaves of a uniform set (34 to 45 targets) left 40 % of
+// the lanes idle.  2^20 uniform: 0.455 -> 0.345 ms (2.5e12 pairs/s); 2^22
+// Plummer, leaves of at most 32: 1.29 -> 1.09 ms; FP64, 262147 uniform: 0.256
+// -> 0.196 ms.  Waves per SIMD: as many as leave no register spilled (a
+// spilled word costs a small box as much as its pairs).  SMALL: for sets whose
+// boxes hold few targets, at most two targets per lane, one wave per SIMD
+// more (2^22 Plummer: 1.09 against 1.15 ms).
+template <typename T, bool SOFT, bool SMALL>
+__global__ void __launch_bounds__(256, sizeof(T) == 8 ? 3 : SMALL ? 6 : 5)
 k_p2p(const Cell* __restrict__ cells, const Root* __restrict__ rootp, Targets tg,
       const int32_t* __restrict__ off, const int32_t* __restrict__ items,
       const typename Vec4<T>::type* __restrict__ P, const T* __restrict__ far, T eps2,
-      O* __restrict__ phi_o, O* __restrict__ ax_o, O* __restrict__ ay_o, O* __restrict__ az_o) {
+      T* __restrict__ phi_o, T* __restrict__ ax_o, T* __restrict__ ay_o, T* __restrict__ az_o) {
     using V = typename Vec4<T>::type;
     __shared__ V shm[4][64];
     __shared__ int owm[4][64];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // (the wave number as a scalar: the box, its list range and the loops over
+    // it then live in scalar registers)
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int li = blockIdx.x * 4 + w;
     if (li >= tg.nbox) return;
     const TBox bx = tg.box[li];
@@ -239,17 +263,37 @@ k_p2p(const Cell* __restrict__ cells, const Root* __restrict__ rootp, Targets tg
     if (bx.leaf >= 0)
         for (int e = e0 + lane; e < e1; e += 64) mine |= items[e] == bx.leaf;
     const bool in_list = __ballot(mine) != 0ull;
-#define P2P_BOX(G)                                                                              \
-    p2p_box<T, O, G, SOFT>(bx, in_list, root, cells, items, e0, e1, P, TP, sh, own, far, tg.n, \
-                           tg.perm, eps2, phi_o, ax_o, ay_o, az_o)
-    if (bx.count <= 8)
-        P2P_BOX(8);
-    else if (bx.count <= 16)
-        P2P_BOX(4);
-    else if (bx.count <= 32)
-        P2P_BOX(2);
-    else
-        P2P_BOX(1);
+#define P2P_BOX(TW, TPL)                                                                       \
+    p2p_box<T, TW, TPL, SOFT>(bx, in_list, root, cells, items, e0, e1, P, TP, sh, own, far,    \
+                              tg.n, tg.perm, eps2, phi_o, ax_o, ay_o, az_o)
+    const int c = bx.count;
+    if constexpr (SMALL) {
+        if (c <= 4)
+            P2P_BOX(4, 1);
+        else if (c <= 8)
+            P2P_BOX(4, 2);
+        else if (c <= 16)
+            P2P_BOX(8, 2);
+        else
+            P2P_BOX(16, 2);
+    } else {
+        if (c <= 8)
+            P2P_BOX(4, 2);
+        else if (c <= 12)
+            P2P_BOX(4, 3);
+        else if (c <= 16)
+            P2P_BOX(4, 4);
+        else if (c <= 24)
+            P2P_BOX(8, 3);
+        else if (c <= 32)
+            P2P_BOX(8, 4);
+        else if (c <= 40)
+            P2P_BOX(8, 5);
+        else if (c <= 48)
+            P2P_BOX(16, 3);
+        else
+            P2P_BOX(16, 4);
+    }
 #undef P2P_BOX
 }
 
@@ -259,19 +303,27 @@ void launch_p2p(const Tree& t, const Targets& tg, int precision, double eps2,
     if (tg.nbox == 0) return;
     dim3 grid((tg.nbox + 3) / 4), block(256);
     const bool soft = eps2 != 0.0;
-#define P2P_LAUNCH(T, SOFT, P)                                                                \
-    hipLaunchKernelGGL((k_p2p<T, T, SOFT>), grid, block, 0, s, t.cells, t.root, tg, src_off, \
-                       src_items, P, (const T*)far, (T)eps2, (T*)phi, (T*)ax, (T*)ay, (T*)az)
+    // small boxes: fewer than 16 targets on average
+    const bool small = tg.n < 16 * (int64_t)tg.nbox;
+#define P2P_LAUNCH(T, SOFT, SMALL, P)                                                        \
+    hipLaunchKernelGGL((k_p2p<T, SOFT, SMALL>), grid, block, 0, s, t.cells, t.root, tg,      \
+                       src_off, src_items, P, (const T*)far, (T)eps2, (T*)phi, (T*)ax,       \
+                       (T*)ay, (T*)az)
     if (precision == HFMM_FP64) {
         if (soft)
-            P2P_LAUNCH(double, true, t.p64);
+            P2P_LAUNCH(double, true, false, t.p64);
         else
-            P2P_LAUNCH(double, false, t.p64);
+            P2P_LAUNCH(double, false, false, t.p64);
+    } else if (small) {
+        if (soft)
+            P2P_LAUNCH(float, true, true, t.p32);
+        else
+            P2P_LAUNCH(float, false, true, t.p32);
     } else {
         if (soft)
-            P2P_LAUNCH(float, true, t.p32);
+            P2P_LAUNCH(float, true, false, t.p32);
         else
-            P2P_LAUNCH(float, false, t.p32);
+            P2P_LAUNCH(float, false, false, t.p32);
     }
 #undef P2P_LAUNCH
     LAUNCH_CHECK();
@@ -309,9 +361,9 @@ k_direct(const typename Vec4<T>::type* __restrict__ src, int64_t ns,
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g = lane / TW, t = lane % TW;
     const int64_t i = (int64_t)blockIdx.x * TW + t;
-    const V me = i < nt ? tgt[i] : V{T(0), T(0), T(0), T(0)};
+    const V q = i < nt ? tgt[i] : V{T(0), T(0), T(0), T(0)};
+    LaneTargets<T, 1> me{{q.x}, {q.y}, {q.z}, {T(0)}, {T(0)}, {T(0)}, {T(0)}};
     V* sh = shm[w];
-    T phi = T(0), ax = T(0), ay = T(0), az = T(0);
     // the next chunk's load is issued before the current chunk's pairs
     int64_t base = (int64_t)w * 64;
     V v = base + lane < ns ? src[base + lane] : p2p_pad<T>();
@@ -321,9 +373,9 @@ k_direct(const typename Vec4<T>::type* __restrict__ src, int64_t ns,
         wave_lds_fence();
         const int64_t k = base + 256 + lane;
         v = k < ns ? src[k] : p2p_pad<T>();
-        p2p_staged<T, G, SOFT, true>(sh, (int)min((int64_t)64, ns - base), g, me.x, me.y, me.z,
-                                     eps2, phi, ax, ay, az);
+        p2p_staged<T, G, 1, SOFT, true>(sh, (int)min((int64_t)64, ns - base), g, eps2, me);
     }
+    T phi = me.phi[0], ax = me.ax[0], ay = me.ay[0], az = me.az[0];
 #pragma unroll
     for (int d = TW; d < 64; d <<= 1) {
         phi += __shfl_xor(phi, d, 64);

@@ -91,3 +91,35 @@ def test_fp32_m2l_split_orders_and_tile_groups(kind, n, leaf, p):
     if kind == "layer":  # the field lies in the plane: its third component is rounding
         out, ref = out[:3], ref[:3]
     assert_close(out, ref, 1e-5, "vs oracle fmm")
+
+
+# ---------------------------------------------------------------- P2P
+# One leaf of n targets against itself (n at and around the lane splits, and
+# above the 64 of one pass), and two-level trees whose lists pack cells into
+# partly filled chunks.  FP64: sums of at most 130 (3000) terms of one sign;
+# FP32: positions rounded to 2^-24 of the leaf against separations above 1e-4.
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-12), ("fp32", 2e-3)])
+@pytest.mark.parametrize("n", [1, 2, 4, 5, 8, 9, 12, 13, 16, 17, 24, 25, 32, 33, 40, 41, 48, 49,
+                               64, 65, 130])
+def test_p2p_single_leaf(n, prec, tol):
+    say(f"p2p one leaf n={n} {prec}")
+    x, y, z, m = W.uniform(n, 71)
+    ref = O.direct(x, y, z, m)
+    out = host(H().solve(*to_dev(x, y, z, m), p=4, method="fmm", precision=prec, leaf_max=n))
+    if n == 1:
+        assert all(float(o[0]) == 0.0 for o in out)
+        return
+    assert_close(out, ref, tol, f"one leaf {prec}")
+
+
+@pytest.mark.parametrize("eps2", [0.0, 1e-4])
+@pytest.mark.parametrize("leaf", [3, 20, 64, 100])
+def test_p2p_depth_one_tree(leaf, eps2):
+    n = 8 * leaf - 3 * (leaf > 3)  # one split, 8 leaves of about `leaf` particles
+    x, y, z, m = W.uniform(n, 72)
+    T = O.Tree(x, y, z, leaf)
+    say(f"p2p n={n} leaf={leaf} eps2={eps2}: depth {T.depth}")
+    ref = T.fmm(m, 6, eps2=eps2)
+    out = host(H().solve(*to_dev(x, y, z, m), p=6, method="fmm", precision="fp64",
+                         leaf_max=leaf, eps2=eps2))
+    assert_close(out, ref, 1e-12, "vs oracle fmm")
