@@ -685,10 +685,23 @@ k_treecode_far(Targets tg, const double4* __restrict__ cen, const int32_t* __res
 //        [-3 Re M21, 3 Im M21, 2 M20]],
 // the same function the degree-by-degree sum evaluates, and its gradient is
 //   D/r^3 + 2 Q.u/r^5 - u (q/r^3 + 3 (D.u)/r^5 + 5 (u.Q.u)/r^7).
-// Per cell: (q, Dx, Dy, Dz), (Qxx, Qyy, Qzz, Qxy), (Qxz, Qyz, 0, 0).
+// Per cell, in units of the root's side S (u = (x - c)/h = (x - c)/S 2^level):
+// D' = D h/S, Q' = 2 Q (h/S)^2, both exact, as (Dx, Dy, Dz, q), (Qxx, Qyy, Qxy,
+// Qxz), Qyz and the FP64 centre (Qzz = -(Qxx + Qyy)): in FP32 one record of 64
+// bytes, so that a wave that gathers 64 cells touches one line per cell.
 // ---------------------------------------------------------------------
+template <typename T>
+struct alignas(sizeof(T) == 4 ? 64 : 32) Cart3 {
+    typename Vec4<T>::type m0, m1;
+    T qyz;
+    double c[3];
+};
+static_assert(sizeof(Cart3<float>) == 64 && sizeof(Cart3<double>) == 96, "Cart3 records");
+
 template <typename TC>
-__global__ void k_cart3(const double* __restrict__ M, int ld, int ncells, TC* __restrict__ C) {
+__global__ void k_cart3(const Cell* __restrict__ cells, const double4* __restrict__ cen,
+                        const double* __restrict__ M, int ld, int ncells,
+                        Cart3<TC>* __restrict__ C) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncells) return;
     const double* X = M + (int64_t)c * ld;
@@ -696,75 +709,78 @@ __global__ void k_cart3(const double* __restrict__ M, int ld, int ncells, TC* __
     const double m11r = X[ridx(1, 1, 0)], m11i = X[ridx(1, 1, 1)];
     const double m20 = X[ridx(2, 0, 0)], m21r = X[ridx(2, 1, 0)], m21i = X[ridx(2, 1, 1)];
     const double m22r = X[ridx(2, 2, 0)], m22i = X[ridx(2, 2, 1)];
-    TC* o = C + (int64_t)c * 12;
-    o[0] = (TC)m00;
-    o[1] = (TC)(-2.0 * m11r);
-    o[2] = (TC)(2.0 * m11i);
-    o[3] = (TC)m10;
-    o[4] = (TC)(6.0 * m22r - m20);
-    o[5] = (TC)(-6.0 * m22r - m20);
-    o[6] = (TC)(2.0 * m20);
-    o[7] = (TC)(-6.0 * m22i);
-    o[8] = (TC)(-3.0 * m21r);
-    o[9] = (TC)(3.0 * m21i);
-    o[10] = TC(0);
-    o[11] = TC(0);
+    const double f = ldexp(1.0, -(int)cells[c].level), f2 = 2.0 * f * f;
+    const double4 x = cen[c];
+    Cart3<TC> o;
+    o.m0 = {(TC)(-2.0 * m11r * f), (TC)(2.0 * m11i * f), (TC)(m10 * f), (TC)m00};
+    o.m1 = {(TC)((6.0 * m22r - m20) * f2), (TC)((-6.0 * m22r - m20) * f2), (TC)(-6.0 * m22i * f2),
+            (TC)(-3.0 * m21r * f2)};
+    o.qyz = (TC)(3.0 * m21i * f2);
+    o.c[0] = x.x;
+    o.c[1] = x.y;
+    o.c[2] = x.z;
+    C[c] = o;
 }
 
-// one evaluation from the moments r0 = (q, D), r1 = (Qxx, Qyy, Qzz, Qxy),
-// r2 = (Qxz, Qyz, -, -) at u (in units of the cell side h, ih = 1/h)
+// One evaluation at v = (x - c)/S from the staged record of the cell (m2: Qyz
+// and the offset).  With e = v.Q'.v / r^2,
+//   f = (q + (D'.v + e/2) / r^2) / r,
+//   grad f = (D' + Q'.v / r^2 - v t) / r^3,  t = q + (3 D'.v + 5/2 e) / r^2.
+// In this order no power of 1/r beyond the third is formed: at the last level
+// (r about 2^-21) the FP32 range still holds them.
 template <typename T, typename V>
-__device__ __forceinline__ void m2p_cart3(const V& r0, const V& r1, const V& r2, T ux, T uy,
-                                          T uz, T ih, T& phi, T& ax, T& ay, T& az) {
-    const T q = r0.x, dx = r0.y, dy = r0.z, dz = r0.w;
-    const T qxx = r1.x, qyy = r1.y, qzz = r1.z, qxy = r1.w, qxz = r2.x, qyz = r2.y;
-    const T r2n = ux * ux + uy * uy + uz * uz;
-    const T ir = rsqrt_fast(r2n), ir2 = ir * ir;
-    const T ir3 = ir * ir2, ir5 = ir3 * ir2, ir7 = ir5 * ir2;
-    const T du = dx * ux + dy * uy + dz * uz;
-    const T qx = qxx * ux + qxy * uy + qxz * uz;
-    const T qy = qxy * ux + qyy * uy + qyz * uz;
-    const T qz = qxz * ux + qyz * uy + qzz * uz;
-    const T uqu = ux * qx + uy * qy + uz * qz;
-    phi += (q * ir + du * ir3 + uqu * ir5) * ih;
-    const T sc = q * ir3 + T(3) * du * ir5 + T(5) * uqu * ir7;
-    const T ih2 = ih * ih;
-    ax += (dx * ir3 + T(2) * qx * ir5 - ux * sc) * ih2;
-    ay += (dy * ir3 + T(2) * qy * ir5 - uy * sc) * ih2;
-    az += (dz * ir3 + T(2) * qz * ir5 - uz * sc) * ih2;
+__device__ __forceinline__ void m2p_cart3(const V& m0, const V& m1, T qyz, T qzz, T vx, T vy,
+                                          T vz, T& phi, T& ax, T& ay, T& az) {
+    const T dx = m0.x, dy = m0.y, dz = m0.z, q = m0.w;
+    const T qxx = m1.x, qyy = m1.y, qxy = m1.z, qxz = m1.w;
+    const T r2 = fma(vx, vx, fma(vy, vy, vz * vz));
+    const T ir = rsqrt_fast(r2), ir2 = ir * ir, ir3 = ir * ir2;
+    const T du = fma(dx, vx, fma(dy, vy, dz * vz));
+    const T qx = fma(qxx, vx, fma(qxy, vy, qxz * vz));
+    const T qy = fma(qxy, vx, fma(qyy, vy, qyz * vz));
+    const T qz = fma(qxz, vx, fma(qyz, vy, qzz * vz));
+    const T e = fma(vx, qx, fma(vy, qy, vz * qz)) * ir2;
+    phi = fma(ir, fma(ir2, fma(T(0.5), e, du), q), phi);
+    const T t = fma(ir2, fma(T(2.5), e, T(3) * du), q);
+    ax = fma(ir3, fma(-t, vx, fma(ir2, qx, dx)), ax);
+    ay = fma(ir3, fma(-t, vy, fma(ir2, qy, dy)), ay);
+    az = fma(ir3, fma(-t, vz, fma(ir2, qz, dz)), az);
 }
+
+// The targets of a lane: offsets from the box's reference point in units of
+// the root's side, and sums.
+template <typename T, int TPL>
+struct FarTargets {
+    T x[TPL], y[TPL], z[TPL];
+    T phi[TPL], ax[TPL], ay[TPL], az[TPL];
+};
 
 // One batch of list cells of a target leaf: lane j (j < B) offers cell k
 // when `valid`; the valid cells are packed at the front of the wave's LDS
-// slice, each as its moments and (r3) the offset from the cell's centre to
-// the leaf's reference point cb in units of the cell side, formed in FP64,
-// with 1/h.  The offset of a target from cell C is then (x - cb) / h_C + r3,
-// one multiply-add per axis from the target's own FP64-formed offset.  Lane
-// g * TW + t (g < G) takes target t and the packed cells g, g + G, ...; the
-// slots past the batch up to the next multiple of G (at most B <= 64, a
-// multiple of G) hold zero moments at unit distance with 1/h = 0, whose
-// terms are exactly zero.  Lanes past G * TW compute on clamped slots and
-// are never summed.
-template <typename T>
-__device__ __forceinline__ void far3_batch(bool valid, int k, const double4& cb,
-                                           const double4* __restrict__ cen,
-                                           const T* __restrict__ C,
-                                           typename Vec4<T>::type* sh, int G, int g, T rx, T ry,
-                                           T rz, T& phi, T& ax, T& ay, T& az) {
+// slice, each as its moments and the offset from the cell's centre to the
+// box's reference point cb in units of the root's side (is = 1/S), formed in
+// FP64.  Lane g * TW + t (g < G) takes targets t, t + TW, .. and the packed
+// cells g, g + G, ...; the slots past the batch up to the next multiple of G
+// (at most B <= 64, a multiple of G) hold zero moments far away, whose terms
+// are exactly zero.  Lanes past G * TW compute on clamped slots and are never
+// summed.
+template <typename T, int TPL>
+__device__ __forceinline__ void far3_batch(bool valid, int k, const double4& cb, double is,
+                                           const Cart3<T>* __restrict__ C,
+                                           typename Vec4<T>::type* sh, int G, int g,
+                                           FarTargets<T, TPL>& me) {
     using V = typename Vec4<T>::type;
     const int lane = threadIdx.x & 63;
     const uint64_t bal = __ballot(valid);
     const int nb = __popcll(bal);
     if (nb == 0) return;  // uniform per wave
-    V r0{}, r1{}, r2{}, r3{};
+    V r0{}, r1{}, r2{};
     if (valid) {
-        const V* ck = (const V*)(C + (int64_t)k * 12);
-        r0 = ck[0];
-        r1 = ck[1];
-        r2 = ck[2];
-        const double4 qc = cen[k];
-        r3 = V{(T)((cb.x - qc.x) * qc.w), (T)((cb.y - qc.y) * qc.w), (T)((cb.z - qc.z) * qc.w),
-               (T)qc.w};
+        const Cart3<T> c = C[k];
+        r0 = c.m0;
+        r1 = c.m1;
+        r2 = V{c.qyz, (T)((cb.x - c.c[0]) * is), (T)((cb.y - c.c[1]) * is),
+               (T)((cb.z - c.c[2]) * is)};
     }
     const int pos = __popcll(bal & lanes_below(lane));
     const int nr = (nb + G - 1) / G * G;
@@ -773,61 +789,68 @@ __device__ __forceinline__ void far3_batch(bool valid, int k, const double4& cb,
         sh[pos] = r0;
         sh[64 + pos] = r1;
         sh[128 + pos] = r2;
-        sh[192 + pos] = r3;
     }
     if (lane >= nb && lane < nr) {
         const V z{};
         sh[lane] = z;
         sh[64 + lane] = z;
-        sh[128 + lane] = z;
-        sh[192 + lane] = V{T(1), T(0), T(0), T(0)};
+        sh[128 + lane] = V{T(0), T(1.2345e15), T(0), T(0)};
     }
     wave_lds_fence();
 #pragma unroll 2
     for (int j0 = 0; j0 < nr; j0 += G) {
         const int j = min(j0 + g, 63);
-        const V a = sh[j], b = sh[64 + j], c = sh[128 + j], d = sh[192 + j];
-        m2p_cart3<T>(a, b, c, rx * d.w + d.x, ry * d.w + d.y, rz * d.w + d.z, d.w, phi, ax,
-                     ay, az);
+        const V a = sh[j], b = sh[64 + j], d = sh[128 + j];
+        const T qzz = -(b.x + b.y);
+#pragma unroll
+        for (int i = 0; i < TPL; ++i)
+            m2p_cart3<T>(a, b, d.x, qzz, me.x[i] + d.y, me.y[i] + d.z, me.z[i] + d.w, me.phi[i],
+                         me.ax[i], me.ay[i], me.az[i]);
     }
 }
 
 // The far field of one target box.  Lane groups are sized to the box:
-// TW = min(count, 64) lanes per group, G = 64 / TW groups (a leaf of 10
-// particles keeps 60 lanes busy where power-of-two groups of 16 kept 40),
-// batches of B = G * (64 / G) cells.  WALK: the M2P cells are read from the
-// FMM lists (the box's CSR items: W, and V for a box without sources; then
-// the V slots of cell b, the box's leaf or its host, and of each ancestor,
-// the non-empty ones queued in the wave's id ring `q` so that every batch
-// but the last is full); otherwise from the box's CSR list items[e0, e1).
-template <typename T, bool WALK>
+// TW = ceil(min(count, 64 TPL) / TPL) lanes of TPL targets per group, G = 64 /
+// TW groups (a leaf of 10 particles keeps 60 lanes busy where power-of-two
+// groups of 16 kept 40), batches of B = G * (64 / G) cells.  WALK: the M2P
+// cells are read from the FMM lists (the box's CSR items: W, and V for a box
+// without sources; then the V slots of cell b, the box's leaf or its host, and
+// of each ancestor, the non-empty ones queued in the wave's id ring `q` so
+// that every batch but the last is full); otherwise from the box's CSR list
+// items[e0, e1).
+template <typename T, bool WALK, int TPL>
 __device__ __forceinline__ void far3_box(const Cell* __restrict__ cells, int b, const TBox& leaf,
-                                          const double4& cb, const double4* __restrict__ cen,
+                                          const double4& cb, double is,
                                           const double4* __restrict__ p64,
                                           const int32_t* __restrict__ items, int e0, int e1,
                                           const int32_t* __restrict__ vsrc,
-                                          const T* __restrict__ C,
+                                          const Cart3<T>* __restrict__ C,
                                           typename Vec4<T>::type* sh, int* q,
                                           T* __restrict__ far, int64_t n) {
     const int lane = threadIdx.x & 63;
-    const int TW = leaf.count < 64 ? leaf.count : 64;
+    const int TW = (min(leaf.count, 64 * TPL) + TPL - 1) / TPL;
     const int G = 64 / TW, B = G * (64 / G);
     const int g = lane / TW, t = lane - g * TW;  // g == G: an idle lane
-    for (int c0 = 0; c0 < leaf.count; c0 += TW) {
-        const bool ok = g < G && c0 + t < leaf.count;
-        const int64_t s = (int64_t)leaf.first + c0 + t;
-        T rx = T(0), ry = T(0), rz = T(0);
-        if (ok) {
-            const double4 pj = p64[s];
-            rx = (T)(pj.x - cb.x);
-            ry = (T)(pj.y - cb.y);
-            rz = (T)(pj.z - cb.z);
+    for (int c0 = 0; c0 < leaf.count; c0 += TW * TPL) {
+        FarTargets<T, TPL> me;
+#pragma unroll
+        for (int i = 0; i < TPL; ++i) {
+            me.x[i] = me.y[i] = me.z[i] = T(0);
+            const int k = c0 + i * TW + t;
+            if (g < G && k < leaf.count) {
+                const double4 pj = p64[leaf.first + k];
+                me.x[i] = (T)((pj.x - cb.x) * is);
+                me.y[i] = (T)((pj.y - cb.y) * is);
+                me.z[i] = (T)((pj.z - cb.z) * is);
+            }
+            me.phi[i] = me.ax[i] = me.ay[i] = me.az[i] = T(0);
         }
-        T phi = T(0), ax = T(0), ay = T(0), az = T(0);
+        auto batch = [&](bool valid, int k) {
+            far3_batch<T, TPL>(valid, k, cb, is, C, sh, G, g, me);
+        };
         for (int eb = e0; eb < e1; eb += B) {
             const bool v = lane < B && eb + lane < e1;
-            far3_batch<T>(v, v ? items[eb + lane] : 0, cb, cen, C, sh, G, g, rx, ry, rz, phi,
-                          ax, ay, az);
+            batch(v, v ? items[eb + lane] : 0);
         }
         if (WALK) {
             // ring of 256 ids: at most B - 1 + 64 <= 127 are queued at once
@@ -843,33 +866,33 @@ __device__ __forceinline__ void far3_box(const Cell* __restrict__ cells, int b, 
                     tail += __popcll(bal);
                     wave_lds_fence();
                     while (tail - head >= B) {
-                        const int kk = q[(head + lane) & 255];
-                        far3_batch<T>(lane < B, kk, cb, cen, C, sh, G, g, rx, ry, rz, phi, ax,
-                                      ay, az);
+                        batch(lane < B, q[(head + lane) & 255]);
                         head += B;
                     }
                 }
             }
-            if (tail > head) {
-                const int kk = q[(head + lane) & 255];
-                far3_batch<T>(lane < tail - head, kk, cb, cen, C, sh, G, g, rx, ry, rz, phi, ax,
-                              ay, az);
+            if (tail > head) batch(lane < tail - head, q[(head + lane) & 255]);
+        }
+        // group 0 adds the other groups' partial sums of its targets
+        const T i1 = (T)is, i2 = (T)(is * is);
+#pragma unroll
+        for (int i = 0; i < TPL; ++i) {
+            T sphi = me.phi[i], sax = me.ax[i], say = me.ay[i], saz = me.az[i];
+            for (int h = 1; h < G; ++h) {
+                const int src = h * TW + (t < TW ? t : 0);
+                sphi += __shfl(me.phi[i], src, 64);
+                sax += __shfl(me.ax[i], src, 64);
+                say += __shfl(me.ay[i], src, 64);
+                saz += __shfl(me.az[i], src, 64);
             }
-        }
-        // group 0 adds the other groups' partial sums of its target
-        T sphi = phi, sax = ax, say = ay, saz = az;
-        for (int h = 1; h < G; ++h) {
-            const int src = h * TW + (t < TW ? t : 0);
-            sphi += __shfl(phi, src, 64);
-            sax += __shfl(ax, src, 64);
-            say += __shfl(ay, src, 64);
-            saz += __shfl(az, src, 64);
-        }
-        if (ok && g == 0) {
-            far[s] = sphi;
-            far[n + s] = sax;
-            far[2 * n + s] = say;
-            far[3 * n + s] = saz;
+            const int k = c0 + i * TW + t;
+            if (g == 0 && k < leaf.count) {
+                const int64_t s = (int64_t)leaf.first + k;
+                far[s] = sphi * i1;
+                far[n + s] = sax * i2;
+                far[2 * n + s] = say * i2;
+                far[3 * n + s] = saz * i2;
+            }
         }
     }
 }
@@ -878,26 +901,35 @@ __device__ __forceinline__ void far3_box(const Cell* __restrict__ cells, int b, 
 // wave per target box, lane groups sized to its target count.  off/items:
 // the box's M2P list (Barnes-Hut), or with WALK its FMM-list part (W, and V
 // for a box without sources), the V lists of the cells above being read
-// from vsrc.
+// from vsrc.  Bound by the VALU issue of the evaluations: 43 slots each in
+// units of the root's side (moments scaled once per cell), where powers of 1/r
+// up to the seventh in units of every cell's own side took 56.  2^22 Plummer:
+// Barnes-Hut lists 14.2 -> 12.4 ms (52 VALU instructions per evaluation with
+// the staging, issued every 3.4 cycles), FMM lists of 2^20 2.25 -> 1.85 ms.
 template <typename T, bool WALK>
-__global__ void __launch_bounds__(256, 6)
+__global__ void __launch_bounds__(256, sizeof(T) == 4 ? 6 : 3)
 k_treecode_far3(const Cell* __restrict__ cells, const Root* __restrict__ root, Targets tg,
-                const double4* __restrict__ cen, const int32_t* __restrict__ off,
-                const int32_t* __restrict__ items, const int32_t* __restrict__ vsrc,
-                const T* __restrict__ C, T* __restrict__ far) {
+                const int32_t* __restrict__ off, const int32_t* __restrict__ items,
+                const int32_t* __restrict__ vsrc, const Cart3<T>* __restrict__ C,
+                T* __restrict__ far) {
     using V = typename Vec4<T>::type;
-    __shared__ V shm[4][256];
+    __shared__ V shm[4][192];
     __shared__ int idq[4][WALK ? 256 : 1];
-    const int w = threadIdx.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = blockIdx.x * 4 + w;
     if (li >= tg.nbox) return;  // uniform per wave
     const TBox bx = tg.box[li];
     if (bx.count <= 0) return;
     const int row = list_row(tg, li, bx);
     const double4 cb = box_ref(*root, bx);
+    const double is = 1.0 / cell_side(*root, 0);
     const int walk_from = bx.leaf >= 0 ? bx.leaf : bx.host;
-    far3_box<T, WALK>(cells, walk_from, bx, cb, cen, tg.p64, items, off[row], off[row + 1], vsrc,
-                      C, shm[w], idq[w], far, tg.n);
+    if (bx.count <= 2)
+        far3_box<T, WALK, 1>(cells, walk_from, bx, cb, is, tg.p64, items, off[row],
+                             off[row + 1], vsrc, C, shm[w], idq[w], far, tg.n);
+    else
+        far3_box<T, WALK, 2>(cells, walk_from, bx, cb, is, tg.p64, items, off[row],
+                             off[row + 1], vsrc, C, shm[w], idq[w], far, tg.n);
 }
 
 __global__ void k_to_float(const double* __restrict__ a, int64_t n, float* __restrict__ b) {
@@ -1240,30 +1272,26 @@ void run_treecode_far(Tree& t, const Targets& tg, int p, bool fp64, bool walk,
     if (tg.n == 0) return;
     const double4* cen = (const double4*)t.cen;
     if (p == 3) {  // quadrupole moments: the Cartesian form
-        const int64_t nel = (int64_t)t.ncells * 12;
         const dim3 grid(grid_for(tg.nbox, 4)), block(256);
 #define FAR3(TT, W)                                                                            \
-    hipLaunchKernelGGL((k_treecode_far3<TT, W>), grid, block, 0, s, t.cells, t.root, tg, cen,   \
-                       off, items, t.vsrc, c, (TT*)far)
-        if (fp64) {
-            double* c = t.arena.down<double>(nel);
-            hipLaunchKernelGGL(k_cart3<double>, dim3(grid_for(t.ncells, 256)), dim3(256), 0, s,
-                               t.M, t.ldm, t.ncells, c);
-            LAUNCH_CHECK();
-            if (walk)
-                FAR3(double, true);
-            else
-                FAR3(double, false);
-        } else {
-            float* c = t.arena.down<float>(nel);
-            hipLaunchKernelGGL(k_cart3<float>, dim3(grid_for(t.ncells, 256)), dim3(256), 0, s,
-                               t.M, t.ldm, t.ncells, c);
-            LAUNCH_CHECK();
-            if (walk)
-                FAR3(float, true);
-            else
-                FAR3(float, false);
-        }
+    hipLaunchKernelGGL((k_treecode_far3<TT, W>), grid, block, 0, s, t.cells, t.root, tg, off,  \
+                       items, t.vsrc, c, (TT*)far)
+#define FAR3_T(TT)                                                                             \
+    {                                                                                          \
+        Cart3<TT>* c = t.arena.down<Cart3<TT>>(t.ncells);                                      \
+        hipLaunchKernelGGL(k_cart3<TT>, dim3(grid_for(t.ncells, 256)), dim3(256), 0, s,        \
+                           t.cells, cen, t.M, t.ldm, t.ncells, c);                             \
+        LAUNCH_CHECK();                                                                        \
+        if (walk)                                                                              \
+            FAR3(TT, true);                                                                    \
+        else                                                                                   \
+            FAR3(TT, false);                                                                   \
+    }
+        if (fp64)
+            FAR3_T(double)
+        else
+            FAR3_T(float)
+#undef FAR3_T
 #undef FAR3
         LAUNCH_CHECK();
         return;
