@@ -123,3 +123,35 @@ def test_p2p_depth_one_tree(leaf, eps2):
     out = host(H().solve(*to_dev(x, y, z, m), p=6, method="fmm", precision="fp64",
                          leaf_max=leaf, eps2=eps2))
     assert_close(out, ref, 1e-12, "vs oracle fmm")
+
+
+# ---------------------------------------------------------------- treecode
+# Barnes-Hut lists and the p = 3 far field on leaves of every size up to and
+# beyond the lanes of a wave, and down to the last levels of the key.
+@pytest.mark.parametrize("kind,n,leaf", [("plummer", 3000, 1), ("plummer", 4001, 3),
+                                         ("uniform", 20000, 70), ("uniform", 9000, 150),
+                                         ("corner", 0, 1)])
+def test_treecode_far_leaf_sizes(kind, n, leaf):
+    if kind == "corner":
+        x, y, z = (np.ascontiguousarray(a) for a in _points(kind).T)
+        m = np.full(len(x), 1.0 / len(x))
+    else:
+        x, y, z, m = W.make(kind, n, 81)
+    say(f"treecode p=3 {kind} n={len(x)} leaf={leaf}")
+    T = O.Tree(x, y, z, leaf)
+    for theta in (0.5, 0.8):
+        ref = O.treecode(x, y, z, m, 3, theta, leaf)
+        t = H().Tree(*to_dev(x, y, z), leaf_max=leaf)
+        t.upward(to_dev(m)[0], 3, H().TREECODE, H().FP64)
+        out = host(t.evaluate(theta=theta))
+        for w in range(2):
+            off, it = T.bh_lists(m, theta, w)
+            goff, git = (a.cpu().numpy() for a in t.bh_list(w))
+            for b in range(T.ncells):
+                assert np.array_equal(np.sort(git[goff[b]:goff[b + 1]]),
+                                      np.sort(it[off[b]:off[b + 1]])), (w, b)
+        assert_close(out, ref, 1e-12, f"theta {theta} fp64")
+        if kind != "corner":  # (there the closest pairs are beyond FP32)
+            out = host(H().solve(*to_dev(x, y, z, m), p=3, method="treecode", theta=theta,
+                                 precision="fp32", leaf_max=leaf))
+            assert_close(out, ref, 2e-5, f"theta {theta} fp32")
