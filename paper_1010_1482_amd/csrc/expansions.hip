@@ -302,31 +302,41 @@ __global__ void k_m2m(const Cell* __restrict__ cells, int c0, int c1,
 // ---------------------------------------------------------------------
 // P2L for the X list (Eq. 3 in the device basis, FP64):
 //   Lt_n^m(B) += sum_j q_j conj(S_n^m((x_j - c_B) / h_B))
-// One 64-lane wave per target cell with an X list (from the compact array
-// of such cells; the others keep LX = 0).  The particles
-// of the cell's X-list leaves are packed into chunks of CH (a lane per list
-// leaf, a scan of the counts, the owner of each slot from wave_run_owner);
-// lane j evaluates
-// particle j of the chunk and stores its P weighted terms in LDS
-// (coefficient-major, so the stores of one term are consecutive), then lane
-// k adds coefficient k (and k + 64, ...) over the chunk: no cross-lane
-// reduction, and every lane is busy however few particles a leaf holds.
-// T: the type of the terms (FP32 for the FP32 path, whose chunks then hold
-// twice as many particles in the same LDS; the sums over chunks are FP64).
+// One 64-lane wave per target cell with an X list (from the compact array of
+// such cells; the others keep LX = 0).  The particles of the cell's X-list
+// leaves are packed into chunks of 64 (a lane per list leaf, a scan of the
+// counts, the owner of each slot from wave_run_owner), lane j evaluating
+// particle j.  The harmonics come order by order (m): the wave stores the
+// weighted terms of one order in LDS, term by term, and its lanes then add
+// them up over the particles, lane g T + t taking the g-th part of the
+// particles of term t (T terms, up to 8 parts), into an FP64 sum per order;
+// the parts are added at the end.  One order's terms are 2 (p - m) reals, so
+// LDS holds 64 particles of them (5 KB at p = 10 in FP32) where it held 20
+// particles of all p^2 terms, and every lane evaluates.
+// T: the type of the terms (FP32 for the FP32 path; the sums are FP64).
 // ---------------------------------------------------------------------
-template <typename T, int NP, int CH, int RS, int KPL>
-__device__ __forceinline__ void p2l_cell(const Cell* __restrict__ cells, int b,
-                                         const int32_t* __restrict__ x_off,
-                                         const int32_t* __restrict__ x_items,
-                                         const double4* __restrict__ cen,
-                                         const double4* __restrict__ p64,
-                                         double* __restrict__ LX, int ld, T* sh, int* own,
-                                         int lane) {
-    constexpr int P = NP * NP;
+constexpr int kP2lStride = 65;  // LDS row stride (bank spread)
+constexpr int p2l_terms(int np, int m) { return m == 0 ? np : 2 * (np - m); }
+constexpr int p2l_parts(int np, int m) {
+    int g = 1;
+    while (g < 8 && 2 * g * p2l_terms(np, m) <= 64) g *= 2;
+    return g;
+}
+
+template <typename T, int NP>
+__global__ void __launch_bounds__(64)
+k_p2l(const Cell* __restrict__ cells, const int32_t* __restrict__ x_cells,
+      const int32_t* __restrict__ x_off, const int32_t* __restrict__ x_items,
+      const double4* __restrict__ cen, const double4* __restrict__ p64,
+      double* __restrict__ LX, int ld) {
+    __shared__ T sh[2 * NP * kP2lStride];
+    __shared__ int own[64];
+    const int lane = threadIdx.x;
+    const int b = x_cells[blockIdx.x];
     const int e0 = x_off[b], e1 = x_off[b + 1];
-    double acc[KPL];
+    double acc[NP];
 #pragma unroll
-    for (int k = 0; k < KPL; ++k) acc[k] = 0.0;
+    for (int m = 0; m < NP; ++m) acc[m] = 0.0;
     const double4 q = cen[b];
     const double ih = q.w;
     for (int eb = e0; eb < e1; eb += 64) {
@@ -338,58 +348,53 @@ __device__ __forceinline__ void p2l_cell(const Cell* __restrict__ cells, int b,
         }
         int tot;
         const int off = wave_excl_scan(cnt, lane, tot);
-        for (int pb = 0; pb < tot; pb += CH) {
-            int o = wave_run_owner(own, off, cnt, pb, CH, lane);
-            const bool ok = lane < CH && pb + lane < tot;
+        for (int pb = 0; pb < tot; pb += 64) {
+            int o = wave_run_owner(own, off, cnt, pb, 64, lane);
+            const bool ok = pb + lane < tot;
             o = ok ? o : 0;
             const int f = __shfl(first, o, 64), fo = __shfl(off, o, 64);
-            const int nv = min(CH, tot - pb);
-            wave_lds_fence();
+            // (lanes past the last particle: a zero weight at unit distance)
+            T ux = T(1), uy = T(0), uz = T(0), w = T(0);
             if (ok) {
                 const double4 pj = p64[f + (pb + lane - fo)];
-                const T w = (T)pj.w;
-                stream_irregular<T, NP>((T)((pj.x - q.x) * ih), (T)((pj.y - q.y) * ih),
-                                        (T)((pj.z - q.z) * ih), [&](int n, int m, T re, T im) {
-                                            sh[ridx(n, m, 0) * RS + lane] = w * re;
-                                            if (m > 0) sh[ridx(n, m, 1) * RS + lane] = -w * im;
-                                        });
+                ux = (T)((pj.x - q.x) * ih);
+                uy = (T)((pj.y - q.y) * ih);
+                uz = (T)((pj.z - q.z) * ih);
+                w = (T)pj.w;
             }
-            wave_lds_fence();
-#pragma unroll
-            for (int kk = 0; kk < KPL; ++kk) {
-                const int k = lane + 64 * kk;
-                if (k < P) {
-                    double a = 0.0;
-                    for (int j = 0; j < nv; ++j) a += (double)sh[k * RS + j];
-                    acc[kk] += a;
+            stream_irregular<T, NP>(ux, uy, uz, [&](int n, int m, T re, T im) {
+                if (m == 0) {
+                    sh[n * kP2lStride + lane] = w * re;
+                } else {
+                    sh[2 * (n - m) * kP2lStride + lane] = w * re;
+                    sh[(2 * (n - m) + 1) * kP2lStride + lane] = -w * im;
                 }
-            }
+                if (n + 1 < NP) return;
+                // the order's terms are complete
+                const int terms = p2l_terms(NP, m), parts = p2l_parts(NP, m), len = 64 / parts;
+                const int t = lane % terms, g = lane / terms;
+                wave_lds_fence();
+                if (g < parts) {
+                    const T* r = sh + t * kP2lStride + g * len;
+                    double a = 0.0;
+#pragma unroll 8
+                    for (int j = 0; j < len; ++j) a += (double)r[j];
+                    acc[m] += a;
+                }
+                wave_lds_fence();
+            });
         }
     }
     double* out = LX + (int64_t)b * ld;
 #pragma unroll
-    for (int kk = 0; kk < KPL; ++kk) {
-        const int k = lane + 64 * kk;
-        if (k < P) out[k] = acc[kk];
+    for (int m = 0; m < NP; ++m) {
+        const int terms = p2l_terms(NP, m), parts = p2l_parts(NP, m);
+        double v = acc[m];
+        for (int g = 1; g < parts; ++g)
+            v += __shfl(acc[m], min(lane + g * terms, 63), 64);
+        if (lane < terms)
+            out[m == 0 ? ridx(lane, 0, 0) : ridx(m + lane / 2, m, lane & 1)] = v;
     }
-    wave_lds_fence();  // the next cell reuses sh and own
-}
-
-template <typename T, int NP>
-__global__ void __launch_bounds__(64)
-k_p2l(const Cell* __restrict__ cells, const int32_t* __restrict__ x_cells,
-      const int32_t* __restrict__ x_off, const int32_t* __restrict__ x_items,
-      const double4* __restrict__ cen, const double4* __restrict__ p64,
-      double* __restrict__ LX, int ld) {
-    constexpr int P = NP * NP;
-    constexpr int PER = 8192 / (int)sizeof(T) / P;     // particles per chunk (<= 9 KB)
-    constexpr int CH = PER < 64 ? PER : 64;
-    constexpr int RS = CH + 1;                         // LDS row stride (bank spread)
-    constexpr int KPL = (P + 63) / 64;                 // coefficients per lane
-    __shared__ T sh[P * RS];
-    __shared__ int own[64];
-    p2l_cell<T, NP, CH, RS, KPL>(cells, x_cells[blockIdx.x], x_off, x_items, cen, p64, LX, ld,
-                                 sh, own, threadIdx.x);
 }
 
 
@@ -440,23 +445,22 @@ __device__ __forceinline__ void m2p_accumulate(const MT* Mc, T ux, T uy, T uz, T
 // the wave's LDS slice (the wave copies the rows with 16-byte loads), and
 // lane g * TW + t evaluates cells g, g + G, ... of the slice at target t.
 // ---------------------------------------------------------------------
-template <int NP, typename MT>
+template <int NP, typename MT, int BYTES = 8192>
 struct FarShape {
     static constexpr int LD = (NP * NP + 15) / 16 * 16;  // row length of M
     // rows staged at once: at most 8 KB of coefficients per wave
-    static constexpr int FB = (8192 / (LD * (int)sizeof(MT))) < 16
-                                  ? (8192 / (LD * (int)sizeof(MT)) < 2 ? 2 : 8192 / (LD * (int)sizeof(MT)))
-                                  : 16;
+    static constexpr int FIT = BYTES / (LD * (int)sizeof(MT));
+    static constexpr int FB = FIT < 2 ? 2 : FIT < 16 ? FIT : 16;
 };
 
-template <typename T, int NP, typename MT, int G>
+template <typename T, int NP, typename MT, int G, int BYTES>
 __device__ __forceinline__ void farp_batch(bool valid, int k, const double4& cb,
                                            const double4* __restrict__ cen,
                                            const MT* __restrict__ M, int32_t* ids,
                                            typename Vec4<T>::type* offs, MT* rows, T rx, T ry,
                                            T rz, T& phi, T& ax, T& ay, T& az) {
     using V = typename Vec4<T>::type;
-    using S = FarShape<NP, MT>;
+    using S = FarShape<NP, MT, BYTES>;
     constexpr int TW = 64 / G, Q = S::LD * (int)sizeof(MT) / 16;  // 16-byte chunks per row
     const int lane = threadIdx.x & 63, g = lane / TW;
     const uint64_t bal = __ballot(valid);
@@ -497,15 +501,17 @@ __device__ __forceinline__ void farp_batch(bool valid, int k, const double4& cb,
 }
 
 // The M2P terms of the box's list items[e0, e1) (the FMM's W list, and V
-// for a box without sources) at its targets.
-template <typename T, int NP, typename MT, int G>
+// for a box without sources) at its targets.  red (kFarLongWaves * 256 of T in
+// LDS): the waves of the block hold parts of one list, and the block's sums
+// are written; otherwise the wave's.
+template <typename T, int NP, typename MT, int G, int BYTES = 8192>
 __device__ __forceinline__ void farp_box(const TBox& leaf, const double4& cb,
                                           const double4* __restrict__ cen,
                                           const double4* __restrict__ p64,
                                           const int32_t* __restrict__ items, int e0, int e1,
                                           const MT* __restrict__ M, int32_t* ids,
                                           typename Vec4<T>::type* offs, MT* rows,
-                                          T* __restrict__ far, int64_t n) {
+                                          T* __restrict__ far, int64_t n, T* red) {
     constexpr int TW = 64 / G;
     const int lane = threadIdx.x & 63, t = lane % TW;
     for (int c0 = 0; c0 < leaf.count; c0 += TW) {
@@ -521,8 +527,8 @@ __device__ __forceinline__ void farp_box(const TBox& leaf, const double4& cb,
         T phi = T(0), ax = T(0), ay = T(0), az = T(0);
         for (int eb = e0; eb < e1; eb += 64) {
             const bool v = eb + lane < e1;
-            farp_batch<T, NP, MT, G>(v, v ? items[eb + lane] : 0, cb, cen, M, ids, offs, rows,
-                                     rx, ry, rz, phi, ax, ay, az);
+            farp_batch<T, NP, MT, G, BYTES>(v, v ? items[eb + lane] : 0, cb, cen, M, ids, offs,
+                                            rows, rx, ry, rz, phi, ax, ay, az);
         }
 #pragma unroll
         for (int d = TW; d < 64; d <<= 1) {
@@ -531,12 +537,29 @@ __device__ __forceinline__ void farp_box(const TBox& leaf, const double4& cb,
             ay += __shfl_xor(ay, d, 64);
             az += __shfl_xor(az, d, 64);
         }
-        if (ok && lane < TW) {
-            far[s] = phi;
-            far[n + s] = ax;
-            far[2 * n + s] = ay;
-            far[3 * n + s] = az;
+        if (!red) {
+            if (ok && lane < TW) {
+                far[s] = phi;
+                far[n + s] = ax;
+                far[2 * n + s] = ay;
+                far[3 * n + s] = az;
+            }
+            continue;
         }
+        T* mine = red + (threadIdx.x >> 6) * 256 + lane;
+        mine[0] = phi;
+        mine[64] = ax;
+        mine[128] = ay;
+        mine[192] = az;
+        __syncthreads();
+        // wave c sums component c
+        const int c = threadIdx.x >> 6;
+        if (c < 4 && ok && lane < TW) {
+            T a = red[64 * c + lane];
+            for (int w = 1; w < (int)(blockDim.x >> 6); ++w) a += red[256 * w + 64 * c + lane];
+            far[c * n + s] = a;
+        }
+        __syncthreads();
     }
 }
 
@@ -605,42 +628,115 @@ __device__ inline double4 box_ref(const Root& r, const TBox& bx) {
     return make_double4(c[0], c[1], c[2], 0.0);
 }
 
+// Lane groups of a box of `count` targets, and whether its list of n cells is
+// a long one: more than `most` evaluations one after the other per lane.
+__host__ __device__ constexpr int farp_groups(int count) {
+    return count <= 4 ? 16 : count <= 8 ? 8 : count <= 16 ? 4 : count <= 32 ? 2 : 1;
+}
+__device__ __forceinline__ bool farp_long(int count, int n, int most) {
+    return n / farp_groups(count) >= most;
+}
+
+#define FARP_GROUPS(C_, F) \
+    if ((C_) <= 4)         \
+        F(16);             \
+    else if ((C_) <= 8)    \
+        F(8);              \
+    else if ((C_) <= 16)   \
+        F(4);              \
+    else if ((C_) <= 32)   \
+        F(2);              \
+    else                   \
+        F(1);
+
 // W-list M2P of the FMM, one wave per target leaf; MT: the multipoles'
 // type (an FP32 copy for the FP32 path).  Short, uneven lists: a wave per
 // leaf replaces the divergent per-particle loops.  (The treecode's long,
 // even lists keep one thread per particle, k_treecode_far: there every lane
 // has a target, while a wave per leaf of ~10 particles leaves lanes idle.)
+// The boxes with long lists are left to k_farp_long.
 template <typename T, int NP, typename MT>
 __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 6 : 1)
 k_farp(const Root* __restrict__ root, Targets tg, const double4* __restrict__ cen,
        const int32_t* __restrict__ off, const int32_t* __restrict__ items,
-       const MT* __restrict__ M, T* __restrict__ far) {
+       const MT* __restrict__ M, int most, T* __restrict__ far) {
     using V = typename Vec4<T>::type;
     using S = FarShape<NP, MT>;
     __shared__ int32_t sid[4][64];
     __shared__ V soff[4][64];
     __shared__ __align__(16) MT srow[4][S::FB * S::LD];
-    const int w = threadIdx.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = blockIdx.x * 4 + w;
     if (li >= tg.nbox) return;  // uniform per wave
     const TBox bx = tg.box[li];
     const int row = list_row(tg, li, bx);
-    const double4 cb = box_ref(*root, bx);
     const int e0 = off[row], e1 = off[row + 1];
+    if (farp_long(bx.count, e1 - e0, most)) return;
+    const double4 cb = box_ref(*root, bx);
 #define FARP_BOX(G)                                                                           \
     farp_box<T, NP, MT, G>(bx, cb, cen, tg.p64, items, e0, e1, M, sid[w], soff[w], srow[w], \
-                           far, tg.n)
-    if (bx.count <= 4)
-        FARP_BOX(16);
-    else if (bx.count <= 8)
-        FARP_BOX(8);
-    else if (bx.count <= 16)
-        FARP_BOX(4);
-    else if (bx.count <= 32)
-        FARP_BOX(2);
-    else
-        FARP_BOX(1);
+                           far, tg.n, (T*)nullptr)
+    FARP_GROUPS(bx.count, FARP_BOX)
 #undef FARP_BOX
+}
+
+// the boxes with long lists, in no particular order (each is summed by itself)
+__global__ void k_farp_find(Targets tg, const int32_t* __restrict__ off, int most,
+                            int32_t* __restrict__ ids, int32_t* __restrict__ count) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, lane = threadIdx.x & 63;
+    bool lng = false;
+    if (i < tg.nbox) {
+        const TBox bx = tg.box[i];
+        const int row = list_row(tg, i, bx);
+        lng = farp_long(bx.count, off[row + 1] - off[row], most);
+    }
+    const uint64_t bal = __ballot(lng);
+    if (!bal) return;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(count, __popcll(bal));
+    at = __shfl(at, 0, 64) + __popcll(bal & lanes_below(lane));
+    if (lng) ids[at] = i;
+}
+
+// Long lists: a block of 8 waves per box, each wave an eighth of the list,
+// summed through LDS in wave order.  These are the large leaves beside finer
+// ones, a few hundred to a few thousand boxes whose lists of 30 to 60 cells a
+// wave would evaluate one after the other.  The grid loops over the boxes
+// found.  W-list M2P, one wave per box -> with this split (4 and more
+// evaluations in a row): 31623 uniform particles, p = 8: 160 -> 64 us; 200003
+// Plummer, p = 10: 335 -> 179 us; 262147 uniform, p = 8, FP64: 514 -> 390 us;
+// but 2^22 Plummer, p = 8: 1.02 -> 1.29 ms, the boxes being enough by
+// themselves: from 2^16 boxes on every list is a wave's own.
+constexpr int kFarLongWaves = 8;
+template <typename T, int NP, typename MT>
+__global__ void __launch_bounds__(64 * kFarLongWaves)
+k_farp_long(const Root* __restrict__ root, Targets tg, const double4* __restrict__ cen,
+            const int32_t* __restrict__ off, const int32_t* __restrict__ items,
+            const MT* __restrict__ M, const int32_t* __restrict__ ids,
+            const int32_t* __restrict__ count, T* __restrict__ far) {
+    using V = typename Vec4<T>::type;
+    constexpr int NW = kFarLongWaves;
+    // rows staged at once: half as many as a wave of k_farp
+    using S = FarShape<NP, MT, 4096>;
+    __shared__ int32_t sid[NW][64];
+    __shared__ V soff[NW][64];
+    __shared__ __align__(16) MT srow[NW][S::FB * S::LD];
+    __shared__ T red[NW * 256];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = *count;
+    for (int k = blockIdx.x; k < n; k += gridDim.x) {
+        const int li = ids[k];
+        const TBox bx = tg.box[li];
+        const int row = list_row(tg, li, bx);
+        const int e0 = off[row], len = off[row + 1] - e0;
+        const int s0 = e0 + len * w / NW, s1 = e0 + len * (w + 1) / NW;
+        const double4 cb = box_ref(*root, bx);
+#define FARP_BOX(G)                                                                         \
+    farp_box<T, NP, MT, G, 4096>(bx, cb, cen, tg.p64, items, s0, s1, M, sid[w], soff[w],    \
+                                 srow[w], far, tg.n, red)
+        FARP_GROUPS(bx.count, FARP_BOX)
+#undef FARP_BOX
+    }
 }
 
 // Treecode far field: M2P over the accepted list of the target's box, one
@@ -932,6 +1028,10 @@ k_treecode_far3(const Cell* __restrict__ cells, const Root* __restrict__ root, T
                              off[row + 1], vsrc, C, shm[w], idq[w], far, tg.n);
 }
 
+__global__ void k_zero_i32(int32_t* __restrict__ p) {
+    if (threadIdx.x == 0) *p = 0;
+}
+
 __global__ void k_to_float(const double* __restrict__ a, int64_t n, float* __restrict__ b) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) b[i] = (float)a[i];
@@ -1186,7 +1286,7 @@ void run_m2l_ops(Tree& t, int p, int layout, void* T, int RB, int KQ, hipStream_
     // several blocks per class for the larger tables (each recomputes the
     // class's small Legendre table)
     const int split = p >= 6 ? 4 : 1;
-    hipLaunchKernelGGL(k_m2l_ops, dim3(343, split), dim3(256), 0, s, p, layout, T, RB, KQ);
+    hipLaunchKernelGGL(k_m2l_ops, dim3(343), dim3(256), 0, s, p, layout, T, RB, KQ);
     LAUNCH_CHECK();
 }
 
@@ -1236,12 +1336,30 @@ void run_far(Tree& t, const Targets& tg, int p, bool fp64, const int32_t* off,
     const bool w = nitems > 0;
     const float* M32 = (!fp64 && w) ? m_as_float(t, s) : nullptr;
     const dim3 grid(grid_for(tg.nbox, 4)), block(256), pgrid(grid_for(tg.n, 256));
+    const dim3 lgrid(std::min(tg.nbox, 1024)), lblock(64 * kFarLongWaves);
     const double4* cen = (const double4*)t.cen;
+    // the boxes with long lists, found on the device
+    const bool split = w && tg.nbox < (1 << 16);
+    const int most = split ? 4 : INT32_MAX;
+    int32_t *lids = nullptr, *lcount = nullptr;
+    if (split) {
+        lcount = t.arena.down<int32_t>(1 + (size_t)tg.nbox);
+        lids = lcount + 1;
+        hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, s, lcount);
+        LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_farp_find, dim3(grid_for(tg.nbox, 256)), block, 0, s, tg, off, most,
+                           lids, lcount);
+        LAUNCH_CHECK();
+    }
 #define FAR_CASE(NP)                                                                          \
     if (fp64) {                                                                               \
-        if (w)                                                                                \
+        if (w) {                                                                              \
+            if (split)                                                                        \
+                hipLaunchKernelGGL((k_farp_long<double, NP, double>), lgrid, lblock, 0, s, t.root,  \
+                               tg, cen, off, items, t.M, lids, lcount, (double*)far);          \
             hipLaunchKernelGGL((k_farp<double, NP, double>), grid, block, 0, s, t.root, tg,     \
-                               cen, off, items, t.M, (double*)far);                            \
+                               cen, off, items, t.M, most, (double*)far);                      \
+        }                                                                                     \
         if (w)                                                                                \
             hipLaunchKernelGGL((k_l2p<double, NP, true>), pgrid, block, 0, s, tg, cen, t.L,     \
                                t.ldm, (double*)far);                                           \
@@ -1249,9 +1367,13 @@ void run_far(Tree& t, const Targets& tg, int p, bool fp64, const int32_t* off,
             hipLaunchKernelGGL((k_l2p<double, NP, false>), pgrid, block, 0, s, tg, cen, t.L,    \
                                t.ldm, (double*)far);                                           \
     } else {                                                                                  \
-        if (w)                                                                                \
+        if (w) {                                                                              \
+            if (split)                                                                        \
+                hipLaunchKernelGGL((k_farp_long<float, NP, float>), lgrid, lblock, 0, s, t.root,    \
+                               tg, cen, off, items, M32, lids, lcount, (float*)far);           \
             hipLaunchKernelGGL((k_farp<float, NP, float>), grid, block, 0, s, t.root, tg, cen,  \
-                               off, items, M32, (float*)far);                                  \
+                               off, items, M32, most, (float*)far);                            \
+        }                                                                                     \
         if (w)                                                                                \
             hipLaunchKernelGGL((k_l2p<float, NP, true>), pgrid, block, 0, s, tg, cen, t.L,      \
                                t.ldm, (float*)far);                                            \

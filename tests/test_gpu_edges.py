@@ -125,6 +125,30 @@ def test_p2p_depth_one_tree(leaf, eps2):
     assert_close(out, ref, 1e-12, "vs oracle fmm")
 
 
+# ---------------------------------------------------------------- W and X lists
+# Leaves of up to 100 particles beside a layer of fine cells: chunks of every
+# fill in P2L, W lists short and long against leaves on either side of 64
+# targets, at the orders where the terms' split over the lanes changes.  FP64
+# as in the other comparisons; FP32 on sets without close pairs.
+@pytest.mark.parametrize("kind,leaf,p,prec", [("layer", 2, 1, "fp64"), ("layer", 7, 2, "fp64"),
+                                              ("layer", 40, 5, "fp64"), ("layer", 100, 8, "fp64"),
+                                              ("layer", 40, 11, "fp64"), ("layer", 20, 16, "fp64"),
+                                              ("plummer", 3, 4, "fp32"), ("plummer", 20, 9, "fp32"),
+                                              ("plummer", 100, 16, "fp32")])
+def test_fmm_w_and_x_lists(kind, leaf, p, prec):
+    if kind == "layer":
+        x, y, z = (np.ascontiguousarray(a) for a in _points(kind).T)
+        m = np.random.default_rng(8).uniform(0.5, 1.5, len(x)) / len(x)
+    else:
+        x, y, z, m = W.make(kind, 6000, 45)
+    T = O.Tree(x, y, z, leaf)
+    longest = [int(np.diff(T.list(w)[0]).max()) for w in (2, 3)]
+    say(f"fmm {prec} {kind} n={len(x)} leaf={leaf} p={p}: longest W, X {longest}")
+    assert min(longest) > 0
+    out = host(H().solve(*to_dev(x, y, z, m), p=p, method="fmm", precision=prec, leaf_max=leaf))
+    assert_close(out, T.fmm(m, p), 1e-12 if prec == "fp64" else 1e-5, "vs oracle fmm")
+
+
 # ---------------------------------------------------------------- treecode
 # Barnes-Hut lists and the p = 3 far field on leaves of every size up to and
 # beyond the lanes of a wave, and down to the last levels of the key.
