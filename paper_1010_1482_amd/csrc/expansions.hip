@@ -1098,9 +1098,9 @@ k_m2l_ops_lp(int p, int pass, int RB, int KQ, int32_t* __restrict__ bexp,
     if (threadIdx.x < HFMM_MAX_P) bmax[threadIdx.x] = INT_MIN;
     const bool far = tab.fill(p, cls);
     const int R = 16 * RB, K = 32 * KQ;
-    const int64_t per = (int64_t)R * K;
-    for (int64_t e = threadIdx.x; e < per; e += blockDim.x) {
-        const int ro = (int)(e / K), ri = (int)(e % K);
+    const int per = R * K;
+    for (int e = blockIdx.y * blockDim.x + threadIdx.x; e < per; e += gridDim.y * blockDim.x) {
+        const int ro = e / K, ri = e % K;
         double val = 0.0;
         int j = 0, n = 0;
         if (far && ro < P && ri < P) {
@@ -1130,12 +1130,15 @@ k_m2l_ops_lp(int p, int pass, int RB, int KQ, int32_t* __restrict__ bexp,
 void run_m2l_ops_lp(int p, int precision, int RB, int KQ, int32_t* bexp, void* hi, void* lo,
                     hipStream_t s) {
     const bool bf = precision == HFMM_M2L_BF16 || precision == HFMM_M2L_BF16X3;
+    // four blocks per class for the larger tables: at p = 12 one left 343 blocks
+    // with 96 entries a thread, 2 x 141 us instead of 2 x 88
+    const int split = p >= 6 ? 4 : 1;
     for (int pass = 0; pass < 2; ++pass) {
         if (bf)
-            hipLaunchKernelGGL((k_m2l_ops_lp<__bf16>), dim3(343), dim3(256), 0, s, p, pass, RB,
-                               KQ, bexp, (__bf16*)hi, (__bf16*)lo);
+            hipLaunchKernelGGL((k_m2l_ops_lp<__bf16>), dim3(343, split), dim3(256), 0, s, p, pass,
+                               RB, KQ, bexp, (__bf16*)hi, (__bf16*)lo);
         else
-            hipLaunchKernelGGL((k_m2l_ops_lp<_Float16>), dim3(343), dim3(256), 0, s, p, pass,
+            hipLaunchKernelGGL((k_m2l_ops_lp<_Float16>), dim3(343, split), dim3(256), 0, s, p, pass,
                                RB, KQ, bexp, (_Float16*)hi, (_Float16*)lo);
         LAUNCH_CHECK();
     }
@@ -1286,7 +1289,7 @@ void run_m2l_ops(Tree& t, int p, int layout, void* T, int RB, int KQ, hipStream_
     // several blocks per class for the larger tables (each recomputes the
     // class's small Legendre table)
     const int split = p >= 6 ? 4 : 1;
-    hipLaunchKernelGGL(k_m2l_ops, dim3(343), dim3(256), 0, s, p, layout, T, RB, KQ);
+    hipLaunchKernelGGL(k_m2l_ops, dim3(343, split), dim3(256), 0, s, p, layout, T, RB, KQ);
     LAUNCH_CHECK();
 }
 
