@@ -55,6 +55,27 @@ def test_list_traversals_deep(kind, leaf):
                                   np.sort(it[off[b]:off[b + 1]])), (w, b)
 
 
+# ---------------------------------------------------------------- sort
+# Around the runs of a wave (256 keys) and the tiles of a block (4096), on a
+# lattice with about ten particles a site: each leaf's particles, and those of
+# a site in their order (the order inside a leaf is free otherwise).
+@pytest.mark.parametrize("n", [2, 63, 65, 255, 257, 511, 4095, 4096, 4097, 5121, 8193])
+def test_sort_tiles(n):
+    rng = np.random.default_rng(n)
+    x, y, z = (np.ascontiguousarray(a) for a in (rng.integers(0, 10, (3, n)) / 9.0))
+    say(f"sort n={n}")
+    T = O.Tree(x, y, z, 64)
+    t = H().Tree(*to_dev(x, y, z), leaf_max=64)
+    gp, op = t.perm().cpu().numpy(), T.perm()
+    cells = T.cells()
+    for a, k, nchild in zip(cells["first"], cells["count"], cells["nchild"]):
+        if nchild == 0:
+            assert np.array_equal(np.sort(gp[a:a + k]), np.sort(op[a:a + k]))
+    site = (9 * x + 100 * 9 * y + 10000 * 9 * z).round().astype(int)[gp]
+    for v in np.unique(site):
+        assert np.all(np.diff(gp[site == v]) > 0)
+
+
 # ---------------------------------------------------------------- direct sum
 # FP64: every term is good to a few 2^-53 and at most 257 of one sign are
 # added, so 257 * 2^-53 < 1e-13 bounds phi; the acceleration's terms cancel by
