@@ -36,7 +36,8 @@ P2P_FLOPS = 21  # per pair: the paper's 19 (Sec. 5.1) plus the potential
 # pair 14 VALU operations (3 sub, 5 fma, 4 mul, 1 max, 1 add), one v_rsq_f32
 # at a quarter of the rate, and a quarter of an instruction of loop
 # overhead: 18.25 issue slots of a 16-lane SIMD, 4 SIMDs per CU, 256 CUs,
-# 2.4 GHz
+# 2.4 GHz.  Where a v_rsq_f32 overlaps the next pair's operations the kernel
+# can pass this rate by a few percent
 P2P_SLOTS = 14 + 4 + 0.25
 P2P_CEILING = 256 * 4 * 16 * 2.4e9 / P2P_SLOTS
 
@@ -518,8 +519,10 @@ def main() -> int:
     # Roofline of the dominant kernel: algorithmic work per launch over the
     # kernel's own device time (HIP events on its stream, averaged over the
     # timed steps).  M2L: 2 p^4 flops per V pair (the real p^2 x p^2
-    # operator), on the matrix cores of its operand type.  P2P: 21 flops per
-    # pair (the paper's count plus the potential) on the FP32 vector units.
+    # operator), on the matrix cores of its operand type; FP32 at p = 8 to 11
+    # runs each product as six BF16 ones, so a sixth of the BF16 peak.  P2P: 21
+    # flops per pair (the paper's count plus the potential) on the FP32 vector
+    # units.
     alu_peak = PEAK["fp64_TFs"] if args.precision == "fp64" else PEAK["fp32_TFs"]
     m2p_evals = 0
     if args.method == "fmm":
@@ -527,8 +530,9 @@ def main() -> int:
     else:
         m2p_evals, pairs = treecode_work(tr)
     m2l_pairs = stats["m2l_pairs"]
-    m2l_peak = {"fp32": PEAK["fp32_TFs"], "fp64": PEAK["fp64_TFs"]}.get(
-        args.precision, PEAK["bf16_TFs"])
+    split = args.precision == "fp32" and 8 <= p <= 11
+    m2l_peak = {"fp32": PEAK["bf16_TFs"] / 6 if split else PEAK["fp32_TFs"],
+                "fp64": PEAK["fp64_TFs"]}.get(args.precision, PEAK["bf16_TFs"])
     cand = {
         "m2l": (ph.get("m2l", 0.0), 2.0 * p ** 4 * m2l_pairs, "mfma", m2l_peak),
         "p2p": (ph.get("p2p", 0.0), P2P_FLOPS * pairs, "alu", alu_peak),
@@ -538,7 +542,8 @@ def main() -> int:
     dom = max(cand, key=lambda k: cand[k][0])
     dms, dwork, dbound, dpeak = cand[dom]
     ach = dwork / (dms * 1e-3) / 1e12
-    m2l_kernel = "k_m2l_valu" if p > (11 if args.precision == "fp64" else 13) else "k_m2l_mma"
+    m2l_kernel = "k_m2l_valu" if p > (11 if args.precision == "fp64" else 13) else \
+        "k_m2l_split" if split else "k_m2l_mma"
     far_kernel = "k_treecode_far3" if p == 3 else "k_treecode_far"
     kname = {"m2l": m2l_kernel, "p2p": "k_p2p", "far": far_kernel}[dom]
     cfg = f"{args.dist}_{n >> 20}M_p{p}_{args.precision}" if n >= 1 << 20 else \
