@@ -20,6 +20,7 @@
 // split in registers, which moves the bytes of the FP32 form, two thirds of
 // what three stored parts would be.
 // Measured, FP32 products -> this form: 2^20 uniform, p = 10: 1.09 -> 0.70 ms
+// (0.78 in long runs of whole evaluations)
 // (1.3 PFLOP/s as executed; a register-only chain of these products on random
 // data runs 1.9); 2^22 Plummer, p = 8: 6.5 -> 4.8 ms.  What bounds it now: the
 // gathered source rows (without them, one row for all: 0.58 and 3.5 ms) and
