@@ -785,6 +785,14 @@ k_treecode_far(Targets tg, const double4* __restrict__ cen, const int32_t* __res
 // D' = D h/S, Q' = 2 Q (h/S)^2, both exact, as (Dx, Dy, Dz, q), (Qxx, Qyy, Qxy,
 // Qxz), Qyz and the FP64 centre (Qzz = -(Qxx + Qyy)): in FP32 one record of 64
 // bytes, so that a wave that gathers 64 cells touches one line per cell.
+// The sums hold q/r^2 with r down to 2^-21, and Q' carries 4^-level: with the
+// masses as they come, both leave the FP32 range for sets whose fields do not
+// (10^6 stars of 2e30 kg within 3e16 m sum to 1e39; masses of 1e-34 make
+// subnormal Q').  So the moments are divided by the power of two next below the
+// largest of them (k_moment_exp: over all cells, since with both signs the
+// root's own may vanish), and the sums get it back, with 1/S and 1/S^2, in FP64
+// where they are stored.  With moments of at most 2 a term is at most 2^43, and
+// the thousands of a list stay 2^70 below the largest FP32 number.
 // ---------------------------------------------------------------------
 template <typename T>
 struct alignas(sizeof(T) == 4 ? 64 : 32) Cart3 {
@@ -794,17 +802,50 @@ struct alignas(sizeof(T) == 4 ? 64 : 32) Cart3 {
 };
 static_assert(sizeof(Cart3<float>) == 64 && sizeof(Cart3<double>) == 96, "Cart3 records");
 
+// maximum over a block of 256 threads, in every thread
+__device__ __forceinline__ int block_max(int v) {
+    __shared__ int wmax[4];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v = max(v, __shfl_xor(v, d, 64));
+    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+}
+
+// Exponent of the largest finite moment of degree <= 2, per block (INT_MIN:
+// none but zeros).  16 lanes per row, so that a wave reads whole lines.
+constexpr int kMomentBlocks = 256;
+__global__ void __launch_bounds__(256)
+k_moment_exp(const double* __restrict__ M, int ld, int ncells, int32_t* __restrict__ part) {
+    const int k = threadIdx.x & 15;
+    int e = INT_MIN;
+    if (k < 9)
+        for (int c = blockIdx.x * 16 + (int)(threadIdx.x >> 4); c < ncells; c += gridDim.x * 16) {
+            const double v = fabs(M[(int64_t)c * ld + k]);
+            if (v > 0.0 && v < HUGE_VAL) e = max(e, ilogb(v));
+        }
+    e = block_max(e);
+    if (threadIdx.x == 0) part[blockIdx.x] = e;
+}
+
+// The records; part: the nparts exponents above; their maximum (0 without a
+// non-zero moment) is written to *mexp.
 template <typename TC>
-__global__ void k_cart3(const Cell* __restrict__ cells, const double4* __restrict__ cen,
-                        const double* __restrict__ M, int ld, int ncells,
-                        Cart3<TC>* __restrict__ C) {
+__global__ void __launch_bounds__(256)
+k_cart3(const Cell* __restrict__ cells, const double4* __restrict__ cen,
+        const double* __restrict__ M, int ld, int ncells, const int32_t* __restrict__ part,
+        int nparts, int32_t* __restrict__ mexp, Cart3<TC>* __restrict__ C) {
+    int e = block_max((int)threadIdx.x < nparts ? part[threadIdx.x] : INT_MIN);
+    if (e == INT_MIN) e = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *mexp = e;
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncells) return;
     const double* X = M + (int64_t)c * ld;
-    const double m00 = X[ridx(0, 0, 0)], m10 = X[ridx(1, 0, 0)];
-    const double m11r = X[ridx(1, 1, 0)], m11i = X[ridx(1, 1, 1)];
-    const double m20 = X[ridx(2, 0, 0)], m21r = X[ridx(2, 1, 0)], m21i = X[ridx(2, 1, 1)];
-    const double m22r = X[ridx(2, 2, 0)], m22i = X[ridx(2, 2, 1)];
+    auto mom = [&](int k) { return ldexp(X[k], -e); };
+    const double m00 = mom(ridx(0, 0, 0)), m10 = mom(ridx(1, 0, 0));
+    const double m11r = mom(ridx(1, 1, 0)), m11i = mom(ridx(1, 1, 1));
+    const double m20 = mom(ridx(2, 0, 0)), m21r = mom(ridx(2, 1, 0)), m21i = mom(ridx(2, 1, 1));
+    const double m22r = mom(ridx(2, 2, 0)), m22i = mom(ridx(2, 2, 1));
     const double f = ldexp(1.0, -(int)cells[c].level), f2 = 2.0 * f * f;
     const double4 x = cen[c];
     Cart3<TC> o;
@@ -823,7 +864,7 @@ __global__ void k_cart3(const Cell* __restrict__ cells, const double4* __restric
 //   f = (q + (D'.v + e/2) / r^2) / r,
 //   grad f = (D' + Q'.v / r^2 - v t) / r^3,  t = q + (3 D'.v + 5/2 e) / r^2.
 // In this order no power of 1/r beyond the third is formed: at the last level
-// (r about 2^-21) the FP32 range still holds them.
+// (r about 2^-21) the FP32 range still holds them, with moments of at most 2.
 template <typename T, typename V>
 __device__ __forceinline__ void m2p_cart3(const V& m0, const V& m1, T qyz, T qzz, T vx, T vy,
                                           T vz, T& phi, T& ax, T& ay, T& az) {
@@ -920,7 +961,7 @@ __device__ __forceinline__ void far3_box(const Cell* __restrict__ cells, int b, 
                                           const double4* __restrict__ p64,
                                           const int32_t* __restrict__ items, int e0, int e1,
                                           const int32_t* __restrict__ vsrc,
-                                          const Cart3<T>* __restrict__ C,
+                                          const Cart3<T>* __restrict__ C, int mexp,
                                           typename Vec4<T>::type* sh, int* q,
                                           T* __restrict__ far, int64_t n) {
     const int lane = threadIdx.x & 63;
@@ -970,7 +1011,7 @@ __device__ __forceinline__ void far3_box(const Cell* __restrict__ cells, int b, 
             if (tail > head) batch(lane < tail - head, q[(head + lane) & 255]);
         }
         // group 0 adds the other groups' partial sums of its targets
-        const T i1 = (T)is, i2 = (T)(is * is);
+        const double i1 = ldexp(is, mexp), i2 = i1 * is;
 #pragma unroll
         for (int i = 0; i < TPL; ++i) {
             T sphi = me.phi[i], sax = me.ax[i], say = me.ay[i], saz = me.az[i];
@@ -984,10 +1025,10 @@ __device__ __forceinline__ void far3_box(const Cell* __restrict__ cells, int b, 
             const int k = c0 + i * TW + t;
             if (g == 0 && k < leaf.count) {
                 const int64_t s = (int64_t)leaf.first + k;
-                far[s] = sphi * i1;
-                far[n + s] = sax * i2;
-                far[2 * n + s] = say * i2;
-                far[3 * n + s] = saz * i2;
+                far[s] = (T)((double)sphi * i1);
+                far[n + s] = (T)((double)sax * i2);
+                far[2 * n + s] = (T)((double)say * i2);
+                far[3 * n + s] = (T)((double)saz * i2);
             }
         }
     }
@@ -1007,7 +1048,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 6 : 3)
 k_treecode_far3(const Cell* __restrict__ cells, const Root* __restrict__ root, Targets tg,
                 const int32_t* __restrict__ off, const int32_t* __restrict__ items,
                 const int32_t* __restrict__ vsrc, const Cart3<T>* __restrict__ C,
-                T* __restrict__ far) {
+                const int32_t* __restrict__ mexp, T* __restrict__ far) {
     using V = typename Vec4<T>::type;
     __shared__ V shm[4][192];
     __shared__ int idq[4][WALK ? 256 : 1];
@@ -1022,10 +1063,10 @@ k_treecode_far3(const Cell* __restrict__ cells, const Root* __restrict__ root, T
     const int walk_from = bx.leaf >= 0 ? bx.leaf : bx.host;
     if (bx.count <= 2)
         far3_box<T, WALK, 1>(cells, walk_from, bx, cb, is, tg.p64, items, off[row],
-                             off[row + 1], vsrc, C, shm[w], idq[w], far, tg.n);
+                             off[row + 1], vsrc, C, *mexp, shm[w], idq[w], far, tg.n);
     else
         far3_box<T, WALK, 2>(cells, walk_from, bx, cb, is, tg.p64, items, off[row],
-                             off[row + 1], vsrc, C, shm[w], idq[w], far, tg.n);
+                             off[row + 1], vsrc, C, *mexp, shm[w], idq[w], far, tg.n);
 }
 
 __global__ void k_zero_i32(int32_t* __restrict__ p) {
@@ -1398,14 +1439,19 @@ void run_treecode_far(Tree& t, const Targets& tg, int p, bool fp64, bool walk,
     const double4* cen = (const double4*)t.cen;
     if (p == 3) {  // quadrupole moments: the Cartesian form
         const dim3 grid(grid_for(tg.nbox, 4)), block(256);
+        const int nparts = std::min(kMomentBlocks, grid_for(t.ncells, 16));
+        int32_t* mexp = t.arena.down<int32_t>(1 + kMomentBlocks);
+        hipLaunchKernelGGL(k_moment_exp, dim3(nparts), block, 0, s, t.M, t.ldm, t.ncells,
+                           mexp + 1);
+        LAUNCH_CHECK();
 #define FAR3(TT, W)                                                                            \
     hipLaunchKernelGGL((k_treecode_far3<TT, W>), grid, block, 0, s, t.cells, t.root, tg, off,  \
-                       items, t.vsrc, c, (TT*)far)
+                       items, t.vsrc, c, mexp, (TT*)far)
 #define FAR3_T(TT)                                                                             \
     {                                                                                          \
         Cart3<TT>* c = t.arena.down<Cart3<TT>>(t.ncells);                                      \
         hipLaunchKernelGGL(k_cart3<TT>, dim3(grid_for(t.ncells, 256)), dim3(256), 0, s,        \
-                           t.cells, cen, t.M, t.ldm, t.ncells, c);                             \
+                           t.cells, cen, t.M, t.ldm, t.ncells, mexp + 1, nparts, mexp, c);     \
         LAUNCH_CHECK();                                                                        \
         if (walk)                                                                              \
             FAR3(TT, true);                                                                    \

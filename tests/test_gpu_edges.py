@@ -200,3 +200,42 @@ def test_treecode_far_leaf_sizes(kind, n, leaf):
             out = host(H().solve(*to_dev(x, y, z, m), p=3, method="treecode", theta=theta,
                                  precision="fp32", leaf_max=leaf))
             assert_close(out, ref, 2e-5, f"theta {theta} fp32")
+
+
+# The FP32 range of the treecodes' far field at p = 3: sums over moments and
+# distances in fixed units must not leave it where the field itself does not.
+# Scaling masses and lengths by powers of two scales every FP32 operation
+# exactly (separations here are above 1e-3, far from the 1e-12 at which P2P
+# starts to round differently), so the scaled results are those of the unscaled
+# set but for the FP64 box geometry's last bits: 1e-6 of the largest value.
+# 20000 stars of 2^108 at 2^55 (a total of 7e36 within 4e16); masses of 1e-34.
+@pytest.mark.parametrize("method", ["treecode", "treecode_fmmlist"])
+@pytest.mark.parametrize("me,le", [(108, 55), (-113, 0), (-20, 20)])
+def test_treecode_fp32_range(method, me, le):
+    x, y, z, _ = W.make("plummer", 20000, 83)
+    m = np.random.default_rng(84).uniform(0.5, 1.5, len(x))
+    say(f"{method} masses 2^{me} lengths 2^{le}")
+
+    def field(a, b):
+        c = 2.0 ** b
+        o = host(H().solve(*to_dev(x * c, y * c, z * c, m * 2.0 ** a), p=3, method=method,
+                           precision="fp32", leaf_max=16))
+        return [o[0] * 2.0 ** (b - a)] + [v * 2.0 ** (2 * b - a) for v in o[1:]]
+
+    assert_close(field(me, le), field(0, 0), 1e-6, "scaled vs unscaled")
+
+
+# Targets far outside a tiny set: only the far field's scale counts (1/S^2 is
+# beyond FP32, the field is not).
+@pytest.mark.parametrize("method", ["treecode", "treecode_fmmlist"])
+def test_treecode_fp32_range_small_lengths(method):
+    x, y, z, m = W.make("plummer", 3000, 85)
+    rng = np.random.default_rng(86)
+    tx, ty, tz = (np.ascontiguousarray(a) for a in rng.uniform(400.0, 900.0, (3, 50)))
+    ref = O.direct_points(x, y, z, m, tx, ty, tz)
+    say(f"{method} lengths 2^-70")
+    c, k = 2.0 ** -70, 2.0 ** -40
+    o = host(H().solve(*to_dev(x * c, y * c, z * c, m * k), p=3, method=method, precision="fp32",
+                       leaf_max=16, targets=to_dev(tx * c, ty * c, tz * c)))
+    # the octupole that p = 3 leaves out: below (20 / 700)^3 of the field
+    assert_close([o[0] * (c / k)] + [v * (c * c / k) for v in o[1:]], ref, 1e-4, "vs direct")
