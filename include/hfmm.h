@@ -115,7 +115,8 @@ enum hfmm_status {
     HFMM_OK = 0,
     HFMM_E_INVAL = -1,       /* bad argument (null pointer, n < 0, ...) */
     HFMM_E_NOMEM = -2,       /* arena too small, see hfmm_required_bytes */
-    HFMM_E_UNSUPPORTED = -3, /* p outside [1, HFMM_MAX_P] or unknown mode */
+    HFMM_E_UNSUPPORTED = -3, /* p outside [1, HFMM_MAX_P], unknown mode, or
+                              * interaction lists beyond 2^31 items */
     HFMM_E_HIP = -4,         /* HIP runtime error */
     HFMM_E_STATE = -5,       /* call order violated (e.g. evaluate before upward) */
     HFMM_E_DATA = -6,        /* non-finite coordinates or masses */

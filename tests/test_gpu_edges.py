@@ -239,3 +239,34 @@ def test_treecode_fp32_range_small_lengths(method):
                        leaf_max=16, targets=to_dev(tx * c, ty * c, tz * c)))
     # the octupole that p = 3 leaves out: below (20 / 700)^3 of the field
     assert_close([o[0] * (c / k)] + [v * (c * c / k) for v in o[1:]], ref, 1e-4, "vs direct")
+
+
+# ---------------------------------------------------------------- list sizes
+# With theta = 0 every box meets every leaf: 50000 leaves of one particle make
+# 2.5e9 P2P items, more than the int32 offsets hold.  Refused from the counts,
+# before anything is written, and the tree goes on with the next evaluation; the
+# same boxes at theta = 0.9 (below the limit, summed in 64 bits too) against the
+# oracle, FP64 as in the other comparisons.
+@pytest.mark.parametrize("nt", [0, 150000])
+def test_bh_lists_beyond_int32_refused(nt):
+    n = 50000
+    x, y, z, m = W.uniform(n, 91)
+    dev = to_dev(x, y, z, m)
+    tp = W.uniform(nt, 92)[:3] if nt else None
+    tg = to_dev(*tp) if nt else None
+    say(f"bh list items beyond int32 nt={nt}")
+    t = H().Tree(*dev[:3], leaf_max=1, max_targets=nt)
+    t.upward(dev[3], 3, H().TREECODE, H().FP64)
+    first = host(t.evaluate(theta=0.9, targets=tg))
+    st = t.stats()
+    assert (st["n_target_boxes"] if nt else n) * n > 2 ** 31
+    with pytest.raises(H().HfmmError) as e:
+        t.evaluate(theta=0.0, targets=tg)
+    assert e.value.code == H().E_UNSUPPORTED
+    out = host(t.evaluate(theta=0.9, targets=tg))
+    assert all(np.array_equal(a, b) for a, b in zip(out, first))
+    ids = W.sample_targets(nt or n, 64, 93)
+    T = O.Tree(x, y, z, 1)
+    ref = (T.treecode_points(m, 3, 0.9, *[c[ids] for c in tp]) if nt
+           else T.treecode(m, 3, 0.9, targets=ids))
+    assert_close([o[ids] for o in out], ref, 1e-12, "theta 0.9 vs oracle")
