@@ -215,6 +215,40 @@ __device__ inline bool is_ancestor_or_self(const Cell& A, const Cell& B) {
     return (B.ix >> s) == A.ix && (B.iy >> s) == A.iy && (B.iz >> s) == A.iz;
 }
 
+// 64-bit sums of gridDim.y arrays of n counts, `stride` apart
+__global__ void __launch_bounds__(256)
+k_sum_counts(const int32_t* __restrict__ cnt, int64_t n, int64_t stride,
+             unsigned long long* __restrict__ tot) {
+    const int32_t* c = cnt + blockIdx.y * stride;
+    unsigned long long v = 0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        v += (unsigned long long)c[i];
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&tot[blockIdx.y], v);
+}
+
+// List offsets are int32, and so are the loops over a row, which step past its
+// end by at most a block: longer lists are refused before they are written.
+constexpr int64_t kMaxListItems = INT32_MAX - 1024;
+
+static void check_list_items(unsigned long long items) {
+    if (items > (unsigned long long)kMaxListItems) throw Status{HFMM_E_UNSUPPORTED};
+}
+
+// The 64-bit totals (on the device) of `arrays` arrays of n counts each, n + 1
+// apart; nullptr when the lists hold at most `most` items and that fits.
+static unsigned long long* list_totals(const int32_t* cnt, int64_t n, int arrays, int64_t most,
+                                       Arena& A, hipStream_t s) {
+    if (most <= kMaxListItems) return nullptr;
+    unsigned long long* tot = A.down<unsigned long long>(arrays);
+    HIP_TRY(hipMemsetAsync(tot, 0, arrays * sizeof(*tot), s));
+    hipLaunchKernelGGL(k_sum_counts, dim3(std::min(512, grid_for(n, 1024)), arrays), dim3(256), 0, s,
+                       cnt, n, n + 1, tot);
+    LAUNCH_CHECK();
+    return tot;
+}
+
 // The list traversals take 32 lanes (half a wave) per cell or target box.
 // They are bound by the latency of their dependent loads (ancestor ->
 // colleagues -> cells; node -> children): one thread per cell made each of
@@ -501,6 +535,7 @@ void build_box_lists(Tree& t, const Targets& tg, int mode, hipStream_t s) {
                        tg, t.coll, t.cflag, t.vsrc, t.x_off, t.x_items, mode, cn, cf, nullptr, nullptr,
                        nullptr, nullptr, t.status);
     LAUNCH_CHECK();
+    const unsigned long long* tot = list_totals(cnt, nb, 2, (int64_t)nb * t.ncells, A, s);
     t.tn_off = A.up<int32_t>(nb + 1);
     t.tf_off = A.up<int32_t>(nb + 1);
     scan_exclusive_i32(cn, t.tn_off, nb, A, s);
@@ -508,7 +543,11 @@ void build_box_lists(Tree& t, const Targets& tg, int mode, hipStream_t s) {
     int32_t h[2];
     HIP_TRY(hipMemcpyAsync(&h[0], t.tn_off + nb, 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(&h[1], t.tf_off + nb, 4, hipMemcpyDeviceToHost, s));
+    unsigned long long long_h[2] = {0, 0};
+    if (tot)
+        HIP_TRY(hipMemcpyAsync(long_h, tot, sizeof(long_h), hipMemcpyDeviceToHost, s));
     stream_wait(s);
+    for (unsigned long long n : long_h) check_list_items(n);
     t.tg_near = h[0];
     t.tg_far = h[1];
     t.tn_items = A.up<int32_t>(std::max<int64_t>(t.tg_near, 1));
@@ -1026,40 +1065,6 @@ __global__ void k_bh_group_starts(const int32_t* __restrict__ flag,
     if (i == nleaves - 1) gstart[gidx[nleaves]] = nleaves;
 }
 
-// 64-bit sums of gridDim.y arrays of n counts, `stride` apart
-__global__ void __launch_bounds__(256)
-k_sum_counts(const int32_t* __restrict__ cnt, int64_t n, int64_t stride,
-             unsigned long long* __restrict__ tot) {
-    const int32_t* c = cnt + blockIdx.y * stride;
-    unsigned long long v = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        v += (unsigned long long)c[i];
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-    if ((threadIdx.x & 63) == 0) atomicAdd(&tot[blockIdx.y], v);
-}
-
-// List offsets are int32, and so are the loops over a row, which step past its
-// end by at most a block: longer lists are refused before they are written.
-constexpr int64_t kMaxListItems = INT32_MAX - 1024;
-
-static void check_list_items(unsigned long long items) {
-    if (items > (unsigned long long)kMaxListItems) throw Status{HFMM_E_UNSUPPORTED};
-}
-
-// The 64-bit totals (on the device) of two arrays of n counts each, n + 1
-// apart; nullptr when the lists of `boxes` rows over ncells cells fit anyway.
-static unsigned long long* list_totals(const int32_t* cnt, int64_t n, int64_t boxes,
-                                       int64_t ncells, Arena& A, hipStream_t s) {
-    if (boxes * ncells <= kMaxListItems) return nullptr;
-    unsigned long long* tot = A.down<unsigned long long>(2);
-    HIP_TRY(hipMemsetAsync(tot, 0, 2 * sizeof(*tot), s));
-    hipLaunchKernelGGL(k_sum_counts, dim3(std::min(512, grid_for(n, 1024)), 2), dim3(256), 0, s,
-                       cnt, n, n + 1, tot);
-    LAUNCH_CHECK();
-    return tot;
-}
-
 // Barnes-Hut lists of the boxes of tg into rows of nrows (+1) offsets:
 // counts, scan, one read-back of the totals, fill
 static void bh_lists_rows(Tree& t, const Targets& tg, double theta, int nrows, int32_t*& a_off,
@@ -1087,7 +1092,7 @@ static void bh_lists_rows(Tree& t, const Targets& tg, double theta, int nrows, i
                        ngroups, t.root, (const double4*)t.cen, theta, ca, cb, nullptr, nullptr,
                        nullptr, nullptr, t.status);
     LAUNCH_CHECK();
-    const unsigned long long* tot = list_totals(cnt, nrows, nb, t.ncells, A, s);
+    const unsigned long long* tot = list_totals(cnt, nrows, 2, (int64_t)nb * t.ncells, A, s);
     a_off = A.up<int32_t>(nrows + 1);
     b_off = A.up<int32_t>(nrows + 1);
     scan_exclusive_i32(ca, a_off, nrows, A, s);

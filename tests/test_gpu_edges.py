@@ -270,3 +270,18 @@ def test_bh_lists_beyond_int32_refused(nt):
     ref = (T.treecode_points(m, 3, 0.9, *[c[ids] for c in tp]) if nt
            else T.treecode(m, 3, 0.9, targets=ids))
     assert_close([o[ids] for o in out], ref, 1e-12, "theta 0.9 vs oracle")
+
+
+# 4e6 boxes with about 190 V cells on each of some seven levels: 3e9 M2P items.
+def test_box_lists_beyond_int32_refused():
+    n, nt = 1 << 21, 1 << 23
+    rng = np.random.default_rng(94)
+    src = to_dev(*rng.random((3, n)))
+    tg = to_dev(*rng.random((3, nt)))
+    say(f"box list items beyond int32 n={n} nt={nt}")
+    t = H().Tree(*src, leaf_max=1, max_targets=nt, arena_bytes_hint=48 << 30)
+    t.upward(torch.ones(n, dtype=torch.float64, device="cuda"), 1, H().TREECODE_FMMLIST,
+             H().FP32)
+    with pytest.raises(H().HfmmError) as e:
+        t.evaluate(targets=tg)
+    assert e.value.code == H().E_UNSUPPORTED
