@@ -734,6 +734,7 @@ int hfmm_export_list(hfmm_tree h, int which, int32_t* off, int32_t* items, void*
     hipStream_t s = (hipStream_t)stream;
     const int nc = t.ncells;
     if (which == 1) {
+        if (t.n_v > INT32_MAX) throw Status{HFMM_E_UNSUPPORTED};
         t.arena.release_temps();
         int32_t* cnt = t.arena.down<int32_t>(nc + 1);
         hipLaunchKernelGGL(k_v_count, dim3(grid_for(nc, 256)), dim3(256), 0, s, t.vsrc, nc, cnt);

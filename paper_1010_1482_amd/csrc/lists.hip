@@ -416,7 +416,8 @@ __global__ void k_list_totals(const int32_t* __restrict__ off, int nc, int32_t* 
 // compact array of the cells with an X list, from the scanned flags
 __global__ void k_x_cells(const int32_t* __restrict__ foff, int nc, int32_t* __restrict__ xc) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < nc && foff[c + 1] > foff[c]) xc[foff[c] - foff[0]] = c;
+    // (the flags follow the V counts in one scan: differences only)
+    if (c < nc && foff[c + 1] != foff[c]) xc[foff[c] - foff[0]] = c;
 }
 
 // ---------------------------------------------------------------------
@@ -671,6 +672,10 @@ void build_fmm_lists(Tree& t, hipStream_t s) {
     scan_exclusive_i32(cnt, off, n4, A, s);
     hipLaunchKernelGGL(k_list_totals, dim3(1), dim3(64), 0, s, off, nc, hr);
     LAUNCH_CHECK();
+    // V lists hold at most 189 cells.  At most 26 cells of one size or larger
+    // touch a cell, so U (its finer pairs counted from the finer side) and W and
+    // X together hold at most (1 + 2 * 26) + 2 * 26 = 105 items per cell.
+    const unsigned long long* tot = list_totals(cnt, nc, 4, (int64_t)189 * nc, A, s);
     t.u_off = off;
     t.w_off = off + (nc + 1);
     t.x_off = off + 2 * (nc + 1);
@@ -692,12 +697,16 @@ void build_fmm_lists(Tree& t, hipStream_t s) {
         radix_sort_pairs(mk3, mv, mk2, t.m2l_torder, nm, 0, 8, A, s);
     }
     std::vector<int32_t> h(5 + kGroups);
+    unsigned long long long_h[4] = {0, 0, 0, 0};
     HIP_TRY(hipMemcpyAsync(h.data(), hr, sizeof(int32_t) * h.size(), hipMemcpyDeviceToHost, s));
+    if (tot)
+        HIP_TRY(hipMemcpyAsync(long_h, tot, sizeof(long_h), hipMemcpyDeviceToHost, s));
     stream_wait(s);
+    check_list_items(long_h[0] + long_h[1] + long_h[2]);  // U, W and X share one array
     t.n_u = h[0];
     t.n_w = h[1];
     t.n_x = h[2];
-    t.n_v = h[3];
+    t.n_v = tot ? (int64_t)long_h[3] : h[3];  // (V rows are not packed)
     t.n_xcells = h[4];
     std::vector<int32_t> gc(h.begin() + 5, h.end());
     int32_t* items = A.up<int32_t>(std::max<int64_t>(t.n_u + t.n_w + t.n_x, 1));

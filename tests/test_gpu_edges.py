@@ -285,3 +285,28 @@ def test_box_lists_beyond_int32_refused():
     with pytest.raises(H().HfmmError) as e:
         t.evaluate(targets=tg)
     assert e.value.code == H().E_UNSUPPORTED
+
+
+# 1.9e7 cells, whose V entries number beyond int32 (they are not packed, so the
+# count is all that could wrap): a cell of the interior has 189.
+def test_v_list_total_beyond_int32():
+    say("V entries beyond int32")
+    # a lattice of 256^3 sites, one particle each, in one cell each of level 8
+    g = (torch.arange(256, dtype=torch.float64, device="cuda") + 0.5) / 256
+    x, y, z = (a.reshape(-1).contiguous() for a in torch.meshgrid(g, g, g, indexing="ij"))
+    # (the root's faces, so that the cells are the lattice's)
+    ends = torch.tensor([0.0, 1.0], dtype=torch.float64, device="cuda")
+    x, y, z = (torch.cat([a, ends]) for a in (x, y, z))
+    t = H().Tree(x, y, z, leaf_max=2, arena_bytes_hint=64 << 30)
+    t.upward(torch.ones_like(x), 1, H().FMM, H().FP32)
+    st = t.stats()
+    # sources within +-3 of a cell per axis that are children of the parents'
+    # neighbours, less the adjacent ones, summed over the cells of a level
+    want = 0
+    for lv in range(2, 9):
+        k = 2 ** lv
+        near = sum(min(k - 1, c + 1) - max(0, c - 1) + 1 for c in range(k))
+        par = sum(min(k, 2 * (c // 2) + 4) - max(0, 2 * (c // 2) - 2) for c in range(k))
+        want += par ** 3 - near ** 3
+    assert st["n_cells"] == sum(8 ** lv for lv in range(9))
+    assert st["list_v"] == want and want > 2 ** 31
