@@ -2,17 +2,26 @@
 // into three BF16 parts.
 //
 // A value is written as a sum of parts h + m + l, each the BF16 rounding of
-// what the parts before it leave: 24 significant bits and a sign in each part,
+// what the parts before it leave: 8 significant bits and a sign in each part,
 // i.e. all of an FP32 value and one bit more of the FP64 operator.  The six
-// products h h, h m, m h, h l, l h, m m are added in FP32; what is dropped is
-// below 2^-26 of h h, a quarter of an FP32 rounding.  BF16 has FP32's exponent
-// range, so nothing is rescaled by level; only the decay of the multipoles
-// with the degree n is moved to the operator (2^mu_n, exact, taken out of one
-// operand and put into the other), so that the low parts stay normal numbers.
-// Error of the potential against the same FMM in FP64 (mean over seeds), FP32
-// matrix products -> this form: 2.07e-7 -> 1.57e-7 (262147 uniform, p = 10),
-// 2.45e-7 -> 1.61e-7 (300007 Plummer, p = 10), 1.80e-7 -> 1.81e-7 (300007
-// uniform, p = 8); the acceleration's is smaller in all.
+// products h h, h m, m h, h l, l h, m m are added in FP32.  |m| <= 2^-8 |h| and
+// |l| <= 2^-17 |h|, so the dropped m l and l m reach 2^-24 of h h, half a
+// rounding of FP32, at worst, and are about 2^-28 of it as a rule.  BF16 has
+// FP32's exponent range, so nothing is rescaled by level; only the decay of the
+// multipoles with the degree n is moved to the operator (2^mu_n, exact, taken
+// out of one operand and put into the other), so that the low parts stay normal
+// numbers (masses of 2^-112 and more: the same range as the FP32 products).
+// Error of the potential against the same FMM in FP64, FP32 matrix products ->
+// this form with all else equal, in 1e-7 (means over six seeds; over 24, good to
+// 1.5 %, for 100003 equal masses at p = 8 and 9):
+//   p                                8            9            10           11
+//   100003 uniform, equal masses  1.40 -> 1.41 1.44 -> 1.44 1.49 -> 1.47 1.52 -> 1.51
+//   100003 uniform, both signs    3.83 -> 2.77 4.07 -> 3.06 5.23 -> 3.87 5.38 -> 3.96
+//   262147 uniform, equal         1.50 -> 1.41 1.53 -> 1.46 1.90 -> 1.55 1.89 -> 1.57
+//   100003 Plummer, equal         1.46 -> 1.47 1.48 -> 1.48 1.65 -> 1.55 1.69 -> 1.56
+//   300007 Plummer, unequal       2.14 -> 1.87 2.06 -> 1.85 3.05 -> 2.13 3.07 -> 2.14
+// (where they agree the error is that of the other phases: the local expansions
+// themselves are as good or better).  Of the acceleration: equal or smaller.
 //
 // At 16 times the rate of the FP32 matrix products six of them cost 3/8.
 // Tiles, teams and segments are those of k_m2l_mma (8 waves of 32 targets of
@@ -65,6 +74,20 @@ __host__ __device__ constexpr SplitShape split_shape(int p) {
 }
 // two operator buffers in LDS when both fit in 144 KiB
 __host__ __device__ constexpr bool split_double(int p) { return 2 * split_shape(p).nch <= 144; }
+// Where the five small part products of a step are added.  Added one by one to
+// the sum of the h h products (kOneSum) they round it six times a step; at p = 8
+// and 9, where the FP32 form has fewest products of its own, the potential's
+// error then came out up to 2.6 % larger than the FP32 form's on some sets.  With
+// a sum of their own it is at most the FP32 form's (the figures above).  Kept to
+// the end of the segment (kLowSum) that sum takes 32 registers at p = 8 (M2L
+// 0.362 -> 0.367 ms at 2^20 uniform, 4.83 -> 4.86 at 2^22 Plummer); at p = 9 its 48
+// spill (0.55 -> 0.74 ms), so each step's sum is added on its own, one output
+// block later, when its products are done (kStepSum: 0.565 -> 0.573 ms, 2^22
+// Plummer 8.1 -> 8.35; at p = 8 0.362 -> 0.378 and 4.83 -> 4.98).
+enum SplitSum { kOneSum, kLowSum, kStepSum };
+__host__ __device__ constexpr SplitSum split_sum(int p) {
+    return p == 8 ? kLowSum : p == 9 ? kStepSum : kOneSum;
+}
 
 // The orders at which this form is the faster one.  M2L at 2^20 uniform, FP32
 // products -> this form, in ms: p = 5 0.18 -> 0.19, p = 6 0.24 -> 0.26, p = 7
@@ -177,6 +200,7 @@ k_m2l_split(const int32_t* __restrict__ tiles, const uint32_t* __restrict__ tmas
     constexpr SplitShape SH = split_shape(P);
     constexpr int RB = SH.rb, KF = SH.kf, TS = SH.ts, NCH = SH.nch, LD4 = SH.ld / 4;
     constexpr bool DB = split_double(P);
+    constexpr SplitSum SUM = split_sum(P);
     constexpr int CB = kSplitCB, NW = kSplitNW, LDO = 16 * RB;
     // the contraction in S steps of 32 elements, the last with the tail
     constexpr int S = KF;
@@ -210,11 +234,14 @@ k_m2l_split(const int32_t* __restrict__ tiles, const uint32_t* __restrict__ tmas
             const int i = (wave * CB + cb) * 16 + col;
             tgt[cb] = i < count ? order[start + i] : -1;
         }
-        floatx4 acc[CB][RB];
+        floatx4 acc[CB][RB], low[CB][SUM == kLowSum ? RB : 1];
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) acc[cb][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int rb = 0; rb < RB; ++rb) {
+                acc[cb][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (SUM == kLowSum) low[cb][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            }
 
         // V entry of position j (every call issues CB loads, past the last slot
         // and for absent targets of an entry that exists), and the row it
@@ -336,6 +363,7 @@ k_m2l_split(const int32_t* __restrict__ tiles, const uint32_t* __restrict__ tmas
             Parts pt[S + 1];
             Raw rt[S + 2];
             Chunks ch[2];
+            floatx4 step[2][CB];  // kStepSum: of this output block and the one before
             pt[0] = p0;
             rt[1] = r1;
             load_chunks(cur, 0, 0, ch[0]);
@@ -364,14 +392,26 @@ k_m2l_split(const int32_t* __restrict__ tiles, const uint32_t* __restrict__ tmas
 #pragma unroll
                         for (int i = 0; i <= sum; ++i)
 #pragma unroll
-                            for (int cb = 0; cb < CB; ++cb)
-                                acc[cb][rb] = mma_bf16(c.m[i], pt[q].m[cb][sum - i], acc[cb][rb]);
+                            for (int cb = 0; cb < CB; ++cb) {
+                                floatx4& a = sum == 0 || SUM == kOneSum ? acc[cb][rb]
+                                             : SUM == kLowSum ? low[cb][SUM == kLowSum ? rb : 0]
+                                                              : step[rb & 1][cb];
+                                const bool first = SUM == kStepSum && sum == 2 && i == 0;
+                                a = mma_bf16(c.m[i], pt[q].m[cb][sum - i], first ? floatx4{} : a);
+                            }
                     if (tail) {
 #pragma unroll
                         for (int i = 0; i < TS; ++i)
 #pragma unroll
                             for (int cb = 0; cb < CB; ++cb)
                                 acc[cb][rb] = mma_bf16(c.t[i], pt[q].t[cb][i], acc[cb][rb]);
+                    }
+                    if constexpr (SUM == kStepSum) {
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb) {
+                            if (rb > 0) acc[cb][rb > 0 ? rb - 1 : 0] += step[~rb & 1][cb];
+                            if (rb == RB - 1) acc[cb][rb] += step[rb & 1][cb];
+                        }
                     }
 #pragma unroll
                     for (int u = rb * units / RB; u < (rb + 1) * units / RB; ++u)
@@ -406,6 +446,10 @@ k_m2l_split(const int32_t* __restrict__ tiles, const uint32_t* __restrict__ tmas
         for (int cb = 0; cb < CB; ++cb) {
             if (tgt[cb] < 0) continue;
             float* o = out + part * part_stride + (int64_t)tgt[cb] * LDO + 4 * g;
+            if constexpr (SUM == kLowSum) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) acc[cb][rb] += low[cb][rb];
+            }
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb)
                 *(float4*)(o + 16 * rb) = make_float4(acc[cb][rb][0], acc[cb][rb][1],

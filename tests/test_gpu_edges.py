@@ -114,6 +114,23 @@ def test_fp32_m2l_split_orders_and_tile_groups(kind, n, leaf, p):
     assert_close(out, ref, 1e-5, "vs oracle fmm")
 
 
+# The potential of both signs cancels to a few percent, so that the M2L's own
+# rounding shows in it: 2.8e-7 to 5.4e-7 over seeds with FP32 matrix products,
+# 1.6e-6 and more when the sources' third BF16 part is lost, 2.2e-6 and more when
+# the operator's is too.
+@pytest.mark.parametrize("p", [8, 9, 10, 11])
+def test_fp32_m2l_split_accuracy(p):
+    n = 100003
+    x, y, z, _ = W.make("uniform", n, 63)
+    m = W.masses(n, 563, "mixed")
+    tg = W.sample_targets(n, 2048, 64)
+    ref = O.fmm(x, y, z, m, p, 64, targets=tg)
+    out = host(H().solve(*to_dev(x, y, z, m), p=p, method="fmm", precision="fp32", leaf_max=64))
+    err = O.rel_l2(out[0][tg], ref[0])
+    say(f"fmm fp32 mixed n={n} p={p}: phi {err:.2e}")
+    assert err < 1e-6
+
+
 # ---------------------------------------------------------------- P2P
 # One leaf of n targets against itself (n at and around the lane splits, and
 # above the 64 of one pass), and two-level trees whose lists pack cells into
