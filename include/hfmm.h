@@ -137,7 +137,9 @@ enum hfmm_status {
  * evaluated at up to n_tgt separate targets at a time (0 for
  * self-evaluation only), at order p.  Host only.  The estimate covers
  * uniform and moderately clustered inputs; a tree that needs more returns
- * HFMM_E_NOMEM. */
+ * HFMM_E_NOMEM.  For HFMM_TREECODE it leaves out the Barnes-Hut lists, whose
+ * length depends on theta (at theta = 0.5 and millions of particles some 9 KB
+ * per leaf; never more than 2^31 entries of 4 bytes). */
 int hfmm_arena_bytes(int64_t n_src, int64_t n_tgt, int leaf_max, int p,
                      int method, int precision, size_t* bytes);
 

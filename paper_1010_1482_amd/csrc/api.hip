@@ -379,12 +379,8 @@ static size_t estimate_bytes(int64_t n_src, int64_t n_tgt, int leaf_max, int p, 
     // fewer for large trees, more for small ones when the arena has room)
     size_t per_cell = 32 + 27 * 4 + 216 * 4 + 3 * 4 + 200 + 16 + 32 + (size_t)ld * 8 * 3 +
                       (size_t)ld * 4 * 2 + (size_t)12 * ld * 4 + 64;
-    // the M2P list of a leaf at theta = 0.5: about 2200 cells (Plummer and
-    // uniform sets of millions), at most all of them; with a shorter estimate
-    // every call on a large set is made twice
-    if (method == HFMM_TREECODE)
-        per_cell = 32 + 32 + 32 + (size_t)P * 8 + 512 + 64 +
-                   (size_t)(4.0 * std::min((double)nc, 2600.0) * n / std::max(1, leaf_max) * 4 / nc);
+    // (the Barnes-Hut lists, whose length goes with theta, are not counted)
+    if (method == HFMM_TREECODE) per_cell = 32 + 32 + 32 + (size_t)P * 8 + 512 + 64;
     // FMM lists and upward data, the FP32 copy of M and the treecode lists:
     // up to 189 M2P items per level from a leaf to the root (levels taken
     // as those of a uniform tree plus two)

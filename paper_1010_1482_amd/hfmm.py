@@ -155,11 +155,34 @@ def _meth(method):
     return METHODS[method] if isinstance(method, str) else int(method)
 
 
-def arena_bytes(n_src, n_tgt=0, leaf_max=64, p=10, method=FMM, precision=FP32):
+def arena_bytes(n_src, n_tgt=0, leaf_max=64, p=10, method=FMM, precision=FP32, theta=None):
+    """The library's estimate; with theta, for the Barnes-Hut treecode, with room
+    for its lists at that acceptance, so that a call on a large set need not be
+    made twice.  Per target box min(all cells, 2500 (0.5 / theta)^2.3) items and
+    3.5 n / leaf_max boxes: Plummer spheres of 2^22 particles have 2350 at theta
+    = 0.5 and 450 at 1.0 (2^20: 7200 at 0.3) in 3.4 n / leaf_max leaves, uniform
+    sets half as many; int32 offsets hold at most 2^31 items."""
     out = C.c_size_t(0)
     _check(_lib().hfmm_arena_bytes(n_src, n_tgt, leaf_max, p, _meth(method), _prec(precision),
                                    C.byref(out)), "hfmm_arena_bytes")
-    return out.value
+    base = out.value
+    if theta is None or _meth(method) != TREECODE:
+        return base
+    leaves = min(n_src, 3.5 * n_src / leaf_max)
+    boxes = min(n_tgt, 2.0 * leaves) if n_tgt else leaves
+    items = min(8.0 / 7.0 * leaves, 2500.0 * (0.5 / max(float(theta), 1e-3)) ** 2.3)
+    lists = 4.0 * min(boxes * items, 2.0 ** 31)
+    return max(base, int(0.8 * (base - (64 << 20)) + lists))
+
+
+def _new_arena(nbytes, least, device):
+    """An arena of nbytes, or of `least` where the device has no room for that."""
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        if least >= nbytes:
+            raise
+    return torch.empty(least, dtype=torch.uint8, device=device)
 
 
 def out_dtype(precision):
@@ -357,18 +380,18 @@ def solve(x, y, z, m, p=10, method=FMM, precision=FP32, leaf_max=64, theta=0.5, 
         return _empty_out(dt, x.device, out)
     if out is None:
         out = tuple(torch.empty(nt, dtype=dt, device=x.device) for _ in range(4))
-    nbytes = arena.numel() if arena is not None else arena_bytes(
-        ns, 0 if targets is None else nt, leaf_max, p, method, precision)
+    if arena is None:
+        size = (ns, 0 if targets is None else nt, leaf_max, p, method, precision)
+        least, nbytes = arena_bytes(*size), arena_bytes(*size, theta=theta)
     for _ in range(6):
-        ar = arena if arena is not None else torch.empty(nbytes, dtype=torch.uint8,
-                                                         device=x.device)
+        ar = arena if arena is not None else _new_arena(nbytes, least, x.device)
         rc = _lib().hfmm_solve(_ptr(x), _ptr(y), _ptr(z), _ptr(m), ns, _ptr(tx), _ptr(ty),
                                _ptr(tz), 0 if targets is None else nt, leaf_max, p,
                                float(theta), method, precision, float(eps2), _ptr(ar),
                                ar.numel(), *[_ptr(o) for o in out], _stream(stream))
         if rc == E_NOMEM and arena is None:
             need = _lib().hfmm_last_required_bytes()
-            nbytes = max(int(need * 1.25), nbytes * 2)
+            least = nbytes = max(int(need * 1.25), ar.numel() * 2)
             continue
         _check(rc, "hfmm_solve")
         return out
@@ -396,14 +419,16 @@ def leapfrog(x, y, z, vx, vy, vz, m, dt, steps, p=10, method=FMM, precision=FP32
     if method == DIRECT:
         sz = C.c_size_t(0)
         _check(_lib().hfmm_direct_bytes(n, 0, precision, C.byref(sz)), "hfmm_direct_bytes")
-        nbytes = sz.value
+        least = nbytes = sz.value
     else:
-        nbytes = arena_bytes(n, 0, leaf_max, p, method, precision)
-    nbytes += 48 * n + (2 << 20)
+        size = (n, 0, leaf_max, p, method, precision)
+        least, nbytes = arena_bytes(*size), arena_bytes(*size, theta=theta)
+    state = 48 * n + (2 << 20)
+    least, nbytes = least + state, nbytes + state
     left = int(steps)
     builds = 0
     for calls in range(1, 9):
-        ar = torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+        ar = _new_arena(nbytes, least, x.device)
         done, nb = C.c_int(0), C.c_int(0)
         rc = _lib().hfmm_leapfrog(_ptr(x), _ptr(y), _ptr(z), _ptr(vx), _ptr(vy), _ptr(vz),
                                   _ptr(m), n, float(dt), left, leaf_max, p, float(theta),
@@ -415,7 +440,7 @@ def leapfrog(x, y, z, vx, vy, vz, m, dt, steps, p=10, method=FMM, precision=FP32
             info.update(builds=builds, calls=calls)
         if rc == E_NOMEM:
             left -= done.value
-            nbytes = max(int(_lib().hfmm_last_required_bytes() * 1.25), nbytes * 2)
+            least = nbytes = max(int(_lib().hfmm_last_required_bytes() * 1.25), ar.numel() * 2)
             continue
         _check(rc, "hfmm_leapfrog")
         return out

@@ -236,13 +236,24 @@ class HipExecutor:
                    for a in (x, y, z, m)]
         prec = hfmm.PRECISIONS[req.precision]
         meth = hfmm.METHODS[req.method]
-        nbytes = hfmm.arena_bytes(req.n, 0, req.leaf_max, req.p, meth, prec)
+        size = (req.n, 0, req.leaf_max, req.p, meth, prec)
+        least = nbytes = hfmm.arena_bytes(*size)
+        # room for Barnes-Hut lists is not part of the admission: charged here
+        # when the budget has it, or else grown to what the call turns out to need
+        want = hfmm.arena_bytes(*size, theta=req.theta)
+        if want > nbytes:
+            try:
+                if req.grow is not None:
+                    req.grow(want - nbytes)
+                nbytes = want
+            except MemoryError:
+                pass
         with torch.cuda.stream(s):
             dev = [h.to(self.device, non_blocking=True) for h in host_in]
             for _ in range(4):
                 # the arena the footprint charged; a larger one only once the
                 # server has charged the difference
-                arena = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+                arena = hfmm._new_arena(nbytes, least, self.device)
                 try:
                     out = hfmm.solve(*dev, p=req.p, method=meth, precision=prec,
                                      leaf_max=req.leaf_max, theta=req.theta, arena=arena,
@@ -255,7 +266,7 @@ class HipExecutor:
                     del arena
                     if req.grow is not None:
                         req.grow(need - nbytes)
-                    nbytes = need
+                    least, nbytes = need, max(need, nbytes)
             else:
                 raise MemoryError("arena did not suffice after growing")
             host_out = [torch.empty(o.shape, dtype=o.dtype, pin_memory=True) for o in out]

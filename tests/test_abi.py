@@ -111,3 +111,27 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"],
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2 and "one GPU" in r.stderr
+
+
+def test_treecode_arena_estimate(lib):
+    from paper_1010_1482_amd import hfmm
+    n = 1 << 22
+    for leaf in (1, 2, 4, 8, 32):
+        base = hfmm.arena_bytes(n, 0, leaf, 3, hfmm.TREECODE, hfmm.FP32)
+        # some 250 bytes per particle and 750 per cell, a quarter more and 64 MB;
+        # the lists, which depend on theta, are no part of it
+        assert base < 1.25 * (300 * n + 800 * (4 * n / leaf + 4096)) + (64 << 20)
+        est = [hfmm.arena_bytes(n, 0, leaf, 3, hfmm.TREECODE, hfmm.FP32, theta=t)
+               for t in (0.0, 0.3, 0.5, 0.8, 1.0, 2.0, float("inf"))]
+        assert est == sorted(est, reverse=True)
+        assert est[-1] == base and est[0] <= base + 4 * 2 ** 31
+    # bytes that whole calls on Plummer spheres took
+    for lg, leaf, theta, need in ((22, 32, 0.5, 4769e6), (22, 32, 0.7, 2458e6),
+                                  (22, 32, 1.0, 1398e6), (22, 8, 1.0, 3684e6),
+                                  (20, 8, 0.5, 3670e6), (20, 32, 0.3, 3429e6),
+                                  (20, 32, 0.5, 1122e6), (18, 8, 0.3, 2638e6),
+                                  (16, 8, 0.3, 458e6), (14, 8, 0.3, 64e6)):
+        est = hfmm.arena_bytes(1 << lg, 0, leaf, 3, "treecode", "fp32", theta=theta)
+        assert need < est < 2.5 * need + (200 << 20), (lg, leaf, theta, est)
+    # other methods know no theta
+    assert hfmm.arena_bytes(n, theta=0.5) == hfmm.arena_bytes(n)

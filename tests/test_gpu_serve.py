@@ -65,3 +65,24 @@ def test_budget_limits_concurrency():
     for _, d, f in ev:
         live += d * f
         assert live <= big
+
+
+@pytest.mark.parametrize("theta,budget", [(1.0, 300 << 20), (0.5, 300 << 20), (0.5, 1 << 30)])
+def test_treecode_request_within_a_tight_budget(theta, budget):
+    # 2^18 uniform particles take 60 MB of arena at theta = 1 and 136 MB at 0.5:
+    # admitted and served, whether or not the budget holds the list estimate
+    need_gpu()
+    from paper_1010_1482_amd import serve
+    n = 1 << 18
+    data = W.uniform(n, 9)
+    req = serve.Request(rid=0, n=n, p=3, t_arrive=0.0, make_inputs=lambda: data,
+                        method="treecode", leaf_max=32, theta=theta, keep_output=True)
+    srv = serve.Server(budget_bytes=budget, slots=1, executor=serve.HipExecutor(1),
+                       footprint=serve.hip_footprint)
+    srv.run([req], realtime=False)
+    say(f"serve treecode theta {theta} budget {budget}: {req.status} {req.error}")
+    assert req.status == "ok" and srv.max_in_use <= budget
+    ids = W.sample_targets(n, 64, 10)
+    ref = O.treecode(*data, 3, theta, 32, targets=ids)
+    e = O.rel_l2(np.stack([o[ids] for o in req.output[1:]]), np.stack(ref[1:]))
+    assert e < 2e-5  # the bar of the other FP32 treecode tests
