@@ -373,6 +373,7 @@ static size_t estimate_bytes(int64_t n_src, int64_t n_tgt, int leaf_max, int p, 
     const int P = p * p;
     int RB, KQ, ld;
     m2l_layout(p, precision, RB, KQ, ld);
+    ld = std::max(ld, round_up(P, 16));  // (the M2L operand's rows may be shorter)
     size_t per_particle = 8 + 4 + 24 + 16 + 32 + 4 + 8 + 4 + 8 + 4 * 8 + 64 + 32;
     // M, L, LX (FP64), the M2L operand and the FP32 copy of M for the
     // far field (FP32), room for twelve M2L partial results (the launch plans

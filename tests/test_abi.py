@@ -135,3 +135,24 @@ def test_treecode_arena_estimate(lib):
         assert need < est < 2.5 * need + (200 << 20), (lg, leaf, theta, est)
     # other methods know no theta
     assert hfmm.arena_bytes(n, theta=0.5) == hfmm.arena_bytes(n)
+
+
+def test_fmm_arena_estimate_counts_whole_rows(lib):
+    # multipoles, local expansions, P2L sums (FP64), an FP32 copy, the M2L
+    # operand (p^2 floats and more) and twelve partial results per cell, in rows
+    # of p^2 numbers padded to 16, a quarter more
+    from paper_1010_1482_amd import hfmm
+    n, leaf = 1 << 20, 64
+    cells = 4 * n // leaf
+    for prec in ("fp32", "fp64", "bf16x3", "fp16"):
+        for p in range(6, 12):
+            ldm = (p * p + 15) // 16 * 16
+            rows = cells * (ldm * (3 * 8 + 4 + 12 * 4) + p * p * 4)
+            # beyond the rows: 224 bytes and more per particle, 1300 per cell
+            est = hfmm.arena_bytes(n, 0, leaf, p, "fmm", prec)
+            assert est >= 1.25 * (rows + 224 * n + 1300 * cells), (prec, p)
+    # an operator table of the same size does not hide it: orders 10 and 9 of
+    # FP32 differ by the rows of 112 and 96 numbers at least
+    d = (hfmm.arena_bytes(n, 0, leaf, 10, "fmm", "fp32") -
+         hfmm.arena_bytes(n, 0, leaf, 9, "fmm", "fp32"))
+    assert d >= 1.25 * cells * 16 * (3 * 8 + 4 + 12 * 4)
