@@ -816,6 +816,9 @@ __device__ inline double dist_point_box(const double p[3], const double lo[3], d
 // except within 1e-12 of equality, where the test itself does, so that the
 // decisions are exactly its own at a third of its instructions (no square
 // root, no selects): 4.1 -> 3.4 ms a pass at N = 2^22 Plummer.  t2 = theta^2.
+// So it does where l^2 overflows (the difference is then NaN or no larger than
+// the bound) and where the squares fall below 1e-280, too close to the subnormal
+// numbers for 1e-12 to bound their error.
 __device__ __forceinline__ bool bh_accept(const double p[3], const double lo[3], double hb,
                                           double side, double theta, double t2) {
     double d2 = 0.0;
@@ -825,7 +828,8 @@ __device__ __forceinline__ bool bh_accept(const double p[3], const double lo[3],
         d2 = fma(e, e, d2);
     }
     const double l2 = side * side, r2 = t2 * d2;
-    if (fabs(l2 - r2) <= 1e-12 * l2) return side < theta * dist_point_box(p, lo, hb);
+    if (!(fabs(l2 - r2) > fma(1e-12, l2, 1e-280)))
+        return side < theta * dist_point_box(p, lo, hb);
     return l2 < r2;
 }
 

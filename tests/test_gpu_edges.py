@@ -327,3 +327,23 @@ def test_v_list_total_beyond_int32():
         want += par ** 3 - near ** 3
     assert st["n_cells"] == sum(8 ** lv for lv in range(9))
     assert st["list_v"] == want and want > 2 ** 31
+
+
+# Lengths whose squares overflow or lose bits: the lists are still those of the
+# acceptance itself, here at 2^-525 and 2^511 times a Plummer sphere.
+@pytest.mark.parametrize("le", [-525, 0, 511])
+def test_bh_lists_at_extreme_lengths(le):
+    x, y, z, m = W.make("plummer", 3000, 87)
+    x, y, z = (a * 2.0 ** le for a in (x, y, z))
+    say(f"bh lists, lengths 2^{le}")
+    T = O.Tree(x, y, z, 1)
+    t = H().Tree(*to_dev(x, y, z), leaf_max=1)
+    t.upward(to_dev(m)[0], 3, H().TREECODE, H().FP64)
+    t.evaluate(theta=0.7)
+    for w in range(2):
+        off, it = T.bh_lists(m, 0.7, w)
+        goff, git = (a.cpu().numpy() for a in t.bh_list(w))
+        assert np.array_equal(goff, off)
+        for b in range(T.ncells):
+            assert np.array_equal(np.sort(git[goff[b]:goff[b + 1]]),
+                                  np.sort(it[off[b]:off[b + 1]])), (w, b)
