@@ -419,17 +419,20 @@ static void direct_t(const double* x, const double* y, const double* z, const do
         LAUNCH_CHECK();
     }
     // the widest target tile that still gives each of the 256 CUs 16 blocks
-    // (8 resident at once; 8 more even out the tail)
-    const int64_t tiles = 16 * 256;
+    // (8 resident at once; 8 more even out the tail); a launch holds less than
+    // 2^32 threads, at 64 targets a block 2^30 targets
+    const int64_t tiles = 16 * 256, most = (int64_t)1 << 29;
 #define DIRECT_LAUNCH(G)                                                                       \
-    {                                                                                          \
-        const dim3 grid((unsigned)((nt + 64 / G - 1) / (64 / G)));                             \
+    for (int64_t t0 = 0; t0 < nt; t0 += most) {                                                \
+        const int64_t n = std::min(most, nt - t0);                                             \
+        const dim3 grid((unsigned)((n + 64 / G - 1) / (64 / G)));                              \
+        T *o0 = (T*)phi + t0, *o1 = (T*)ax + t0, *o2 = (T*)ay + t0, *o3 = (T*)az + t0;         \
         if (eps2 != 0.0)                                                                       \
-            hipLaunchKernelGGL((k_direct<T, G, true>), grid, dim3(256), 0, s, src, ns, tgt, nt, \
-                               (T)eps2, (T*)phi, (T*)ax, (T*)ay, (T*)az);                      \
+            hipLaunchKernelGGL((k_direct<T, G, true>), grid, dim3(256), 0, s, src, ns,         \
+                               tgt + t0, n, (T)eps2, o0, o1, o2, o3);                          \
         else                                                                                   \
-            hipLaunchKernelGGL((k_direct<T, G, false>), grid, dim3(256), 0, s, src, ns, tgt,   \
-                               nt, (T)eps2, (T*)phi, (T*)ax, (T*)ay, (T*)az);                  \
+            hipLaunchKernelGGL((k_direct<T, G, false>), grid, dim3(256), 0, s, src, ns,        \
+                               tgt + t0, n, (T)eps2, o0, o1, o2, o3);                          \
     }
     if (nt >= 64 * tiles)
         DIRECT_LAUNCH(1)

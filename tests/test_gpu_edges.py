@@ -94,6 +94,24 @@ def test_direct_target_tiles(nt, ns, prec, tol):
     assert_close(out, ref, tol, f"direct {prec}")
 
 
+# More targets than one launch of 64 a block holds (2^30), on a line beside
+# three sources; around the seams and the end.  FP32: coordinates below 7 rounded
+# to 2^-24 of themselves and separations above 3, so a few 1e-7 per term.
+def test_direct_beyond_one_launch():
+    nt = (1 << 30) + 5
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 80 GB of device memory")
+    say(f"direct nt={nt}")
+    line = torch.arange(nt, dtype=torch.float64, device="cuda").mul_(2.0 ** -28)
+    src = [np.array(v) for v in ([-1.0, -2.0, -1.5], [-1.0, 5.0, 6.0], [-3.0, -1.0, 7.0],
+                                 [0.5, 1.0, 0.25])]
+    ids = np.r_[0:3, (1 << 29) - 3:(1 << 29) + 3, (1 << 30) - 3:nt]
+    out = H().direct(*to_dev(*src), precision="fp32", targets=(line, line, line))
+    out = host([o[torch.from_numpy(ids).cuda()] for o in out])
+    c = ids * 2.0 ** -28
+    assert_close(out, O.direct_points(*src, c, c, c), 1e-5, "beyond one launch")
+
+
 # ---------------------------------------------------------------- FP32 M2L
 # FP32 against the FP64 evaluation of the same approximation: the bar of the
 # other FP32 tests.  Small leaves give many cells: 32 and more 256-target tiles
