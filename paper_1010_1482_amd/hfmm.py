@@ -158,21 +158,27 @@ def _meth(method):
 def arena_bytes(n_src, n_tgt=0, leaf_max=64, p=10, method=FMM, precision=FP32, theta=None):
     """The library's estimate; with theta, for the Barnes-Hut treecode, with room
     for its lists at that acceptance, so that a call on a large set need not be
-    made twice.  Per target box min(all cells, 2500 (0.5 / theta)^2.3) items and
-    3.5 n / leaf_max boxes: Plummer spheres of 2^22 particles have 2350 at theta
-    = 0.5 and 450 at 1.0 (2^20: 7200 at 0.3) in 3.4 n / leaf_max leaves, uniform
-    sets half as many; int32 offsets hold at most 2^31 items."""
+    made twice."""
+    return _arena_sizes(n_src, n_tgt, leaf_max, p, _meth(method), _prec(precision), theta)[1]
+
+
+def _arena_sizes(n_src, n_tgt, leaf_max, p, method, precision, theta):
+    """The library's estimate without and with the Barnes-Hut lists.  Per target
+    box min(all cells, 2500 (0.5 / theta)^2.3) items and 3.5 n / leaf_max boxes:
+    Plummer spheres of 2^22 particles have 2350 at theta = 0.5 and 450 at 1.0
+    (2^20: 7200 at 0.3) in 3.4 n / leaf_max leaves, uniform sets half as many;
+    int32 offsets hold at most 2^31 items."""
     out = C.c_size_t(0)
-    _check(_lib().hfmm_arena_bytes(n_src, n_tgt, leaf_max, p, _meth(method), _prec(precision),
-                                   C.byref(out)), "hfmm_arena_bytes")
+    _check(_lib().hfmm_arena_bytes(n_src, n_tgt, leaf_max, p, method, precision, C.byref(out)),
+           "hfmm_arena_bytes")
     base = out.value
-    if theta is None or _meth(method) != TREECODE:
-        return base
+    if theta is None or method != TREECODE:
+        return base, base
     leaves = min(n_src, 3.5 * n_src / leaf_max)
     boxes = min(n_tgt, 2.0 * leaves) if n_tgt else leaves
     items = min(8.0 / 7.0 * leaves, 2500.0 * (0.5 / max(float(theta), 1e-3)) ** 2.3)
     lists = 4.0 * min(boxes * items, 2.0 ** 31)
-    return max(base, int(0.8 * (base - (64 << 20)) + lists))
+    return base, max(base, int(0.8 * (base - (64 << 20)) + lists))
 
 
 def _new_arena(nbytes, least, device):
@@ -381,8 +387,8 @@ def solve(x, y, z, m, p=10, method=FMM, precision=FP32, leaf_max=64, theta=0.5, 
     if out is None:
         out = tuple(torch.empty(nt, dtype=dt, device=x.device) for _ in range(4))
     if arena is None:
-        size = (ns, 0 if targets is None else nt, leaf_max, p, method, precision)
-        least, nbytes = arena_bytes(*size), arena_bytes(*size, theta=theta)
+        least, nbytes = _arena_sizes(ns, 0 if targets is None else nt, leaf_max, p, method,
+                                     precision, theta)
     for _ in range(6):
         ar = arena if arena is not None else _new_arena(nbytes, least, x.device)
         rc = _lib().hfmm_solve(_ptr(x), _ptr(y), _ptr(z), _ptr(m), ns, _ptr(tx), _ptr(ty),
@@ -421,8 +427,7 @@ def leapfrog(x, y, z, vx, vy, vz, m, dt, steps, p=10, method=FMM, precision=FP32
         _check(_lib().hfmm_direct_bytes(n, 0, precision, C.byref(sz)), "hfmm_direct_bytes")
         least = nbytes = sz.value
     else:
-        size = (n, 0, leaf_max, p, method, precision)
-        least, nbytes = arena_bytes(*size), arena_bytes(*size, theta=theta)
+        least, nbytes = _arena_sizes(n, 0, leaf_max, p, method, precision, theta)
     state = 48 * n + (2 << 20)
     least, nbytes = least + state, nbytes + state
     left = int(steps)
