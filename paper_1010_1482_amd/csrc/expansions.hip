@@ -704,9 +704,13 @@ __global__ void k_farp_find(Targets tg, const int32_t* __restrict__ off, int mos
 // wave would evaluate one after the other.  The grid loops over the boxes
 // found.  W-list M2P, one wave per box -> with this split (4 and more
 // evaluations in a row): 31623 uniform particles, p = 8: 160 -> 64 us; 200003
-// Plummer, p = 10: 335 -> 179 us; 262147 uniform, p = 8, FP64: 514 -> 390 us;
-// but 2^22 Plummer, p = 8: 1.02 -> 1.29 ms, the boxes being enough by
-// themselves: from 2^16 boxes on every list is a wave's own.
+// Plummer, p = 10: 335 -> 179 us; 262147 uniform, p = 8, FP64: 514 -> 390 us.
+// From 2^16 boxes on every list is a wave's own, the boxes being enough by
+// themselves.  Around that line the split still gains on Plummer spheres and
+// loses where many boxes have middling lists (far field at p = 8 in FP32 without
+// -> with it, us): Plummer 30367 boxes 335 -> 251, 41066 461 -> 330, 64760 577
+// -> 467, 108973 750 -> 699; uniform 112313 (9 cells a list) 664 -> 838; Plummer
+// of 4.4e5 1020 -> 1290.
 constexpr int kFarLongWaves = 8;
 template <typename T, int NP, typename MT>
 __global__ void __launch_bounds__(64 * kFarLongWaves)
@@ -1050,9 +1054,10 @@ __device__ __forceinline__ void far3_box(const Cell* __restrict__ cells, int b, 
 // for a box without sources), the V lists of the cells above being read
 // from vsrc.  Bound by the VALU issue of the evaluations: 43 slots each in
 // units of the root's side (moments scaled once per cell), where powers of 1/r
-// up to the seventh in units of every cell's own side took 56.  2^22 Plummer:
-// Barnes-Hut lists 14.2 -> 12.4 ms (52 VALU instructions per evaluation with
-// the staging, issued every 3.4 cycles), FMM lists of 2^20 2.25 -> 1.85 ms.
+// up to the seventh in units of every cell's own side took 56.  In whole
+// evaluations, 2^22 Plummer, Barnes-Hut lists 14.2 -> 11.7 to 13.1 ms between
+// runs (52 VALU instructions per evaluation with the staging, issued every 3.4
+// cycles), FMM lists of 2^20 2.21 -> 1.81 ms.
 template <typename T, bool WALK>
 __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 6 : 3)
 k_treecode_far3(const Cell* __restrict__ cells, const Root* __restrict__ root, Targets tg,

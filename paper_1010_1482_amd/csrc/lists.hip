@@ -742,10 +742,16 @@ void build_fmm_lists(Tree& t, hipStream_t s) {
     // without a tile, more than the 1 in 8 that the shared reads could repay;
     // and below 32 groups (one for each team of the 256 CUs) a team's run of
     // slots is shorter than a group and its octants' shares of it differ by a
-    // few percent.  Measured, groups of 8 against 1, FP32 unless noted: 2^20
-    // uniform, p = 10 (19 groups) 0.71 against 0.69 ms; 2^22 Plummer, p = 8
-    // (248 groups) 4.8 against 5.1 ms; 2^22 uniform, p = 12, BF16x3 (146
-    // groups) 7.7 against 8.0 ms.
+    // few percent.  Measured, M2L with groups of 8 against 1 in ms, by tiles an
+    // octant:
+    //                 FP32 p = 8     FP32 p = 10    BF16x3 p = 10  FP64 p = 8
+    //   10 (uniform)  0.205 0.212    0.417 0.415    0.304 0.316    0.530 0.516
+    //   18 (uniform)  0.359 0.354    0.737 0.724    0.546 0.612    0.933 0.911
+    //   36 (Plummer)  0.693 0.710    1.387 1.427    1.092 1.250    1.796 1.781
+    //   60 (uniform)  1.008 1.045    2.123 2.192    1.601 2.058    2.707 2.638
+    //   72 (Plummer)  1.386 1.421    3.014 3.147    2.252 3.003    3.478 3.603
+    //  248 (Plummer)  4.8   5.1
+    // (BF16x3, which reads two rows per source, would gain from 18 on.)
     std::vector<int32_t>& tiles = t.m2l_tiles_h;
     tiles.clear();
     int ocount[8] = {0}, ostart[9] = {0};

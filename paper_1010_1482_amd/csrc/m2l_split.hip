@@ -28,13 +28,17 @@
 // one octant, all output rows); the sources are gathered as FP32 rows and
 // split in registers, which moves the bytes of the FP32 form, two thirds of
 // what three stored parts would be.
-// Measured, FP32 products -> this form: 2^20 uniform, p = 10: 1.09 -> 0.70 ms
-// (0.78 in long runs of whole evaluations)
-// (1.3 PFLOP/s as executed; a register-only chain of these products on random
-// data runs 1.9); 2^22 Plummer, p = 8: 6.5 -> 4.8 ms.  What bounds it now: the
-// gathered source rows (without them, one row for all: 0.58 and 3.5 ms) and
-// the barrier of every slot; 64 targets per wave with half the operator reads
-// (4 waves, 512 registers) were slower, 0.83 and 5.1 ms.
+// Measured in whole evaluations, FP32 products -> this form: 2^20 uniform, p =
+// 10: 1.15 -> 0.73 to 0.77 ms between runs (0.70 in a loop of its own: 1.3
+// PFLOP/s as executed; a register-only chain of these products on random data
+// runs 1.9); 2^22 Plummer, p = 8: 6.7 -> 4.85 to 5.0 ms.  What bounds it now: at
+// 2^20, p = 10 the 4.1 GB a launch fetches from beyond L2 (source rows and
+// operators, L2 hit rate 0.44), 5.2 TB/s, the rate of a large copy, with the
+// matrix cores busy 54 % of the time; at 2^22 Plummer 10.9 GB (hit rate 0.74, 2
+// TB/s) and 43 %: the latency of the gathered rows and the barrier of every slot
+// (without the gather, one row for all: 0.58 and 3.5 ms).  64 targets per wave
+// with half the operator reads (4 waves, 512 registers) were slower, 0.83 and
+// 5.1 ms.
 //
 // v_mfma_f32_16x16x32_bf16: lane group g = lane / 16 feeds the contraction
 // elements 32 q + 8 g .. + 7 of its column (target) and row (operator).  The
@@ -91,7 +95,7 @@ __host__ __device__ constexpr SplitSum split_sum(int p) {
 
 // The orders at which this form is the faster one.  M2L at 2^20 uniform, FP32
 // products -> this form, in ms: p = 5 0.18 -> 0.19, p = 6 0.24 -> 0.26, p = 7
-// 0.35 -> 0.34, p = 8 0.47 -> 0.34, p = 9 0.80 -> 0.54, p = 10 1.04 -> 0.71,
+// 0.35 -> 0.34, p = 8 0.47 -> 0.37, p = 9 0.80 -> 0.57, p = 10 1.04 -> 0.71,
 // p = 11 1.54 -> 0.94, p = 12 2.08 -> 2.50.  Below, two blocks of the FP32
 // kernel share a CU, and the slots are too short to hide the splitting; at 12
 // the operator (144 KB) leaves one LDS buffer, and the registers that stage

@@ -231,9 +231,9 @@ __device__ __forceinline__ void p2p_box(const TBox& bx, bool in_list, const Root
 // (TW of 4, 8 or 16, the TPL that covers the box) leaves at most TW - 1 of
 // TW * TPL target slots empty: with one target per lane and TW = 64 beyond 32
 // targets, half of the leaves of a uniform set (34 to 45 targets) left 40 % of
-// the lanes idle.  2^20 uniform: 0.455 -> 0.345 ms (2.5e12 pairs/s); 2^22
-// Plummer, leaves of at most 32: 1.29 -> 1.09 ms; FP64, 262147 uniform: 0.256
-// -> 0.196 ms.  Waves per SIMD: as many as leave no register spilled (a
+// the lanes idle.  In whole evaluations: 2^20 uniform 0.495 -> 0.39 ms (2.2e12
+// pairs/s); 2^22 Plummer, leaves of at most 32, 1.31 -> 1.10 ms; FP64, 262147
+// uniform, 0.252 -> 0.211 ms.  Waves per SIMD: as many as leave no register spilled (a
 // spilled word costs a small box as much as its pairs).  SMALL: for sets whose
 // boxes hold few targets, at most two targets per lane, one wave per SIMD
 // more (2^22 Plummer: 1.09 against 1.15 ms).
